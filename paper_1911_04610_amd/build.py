@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 OUT = os.path.join(HERE, "libxpipe.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["k_optim.hip", "k_gemm.hip", "k_elem.hip", "stage.cpp"]
+SOURCES = ["k_optim.hip", "k_gemm.hip", "k_conv.hip", "k_elem.hip", "stage.cpp"]
 ARCH = "gfx950"
 
 
@@ -50,7 +50,7 @@ def build(verbose=False):
             print(msg)
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(4, os.cpu_count() or 1)) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     tmp = OUT + ".tmp"
     cmd = [hipcc, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp] + objs

@@ -1,0 +1,593 @@
+// bf16 implicit-GEMM convolution on CDNA4 MFMA, operands copied from memory
+// straight into LDS (forward and data gradient, 16-byte chunk path).
+//
+// What it computes is ConvArgs' definition (xp_kernels.h); the general kernel
+// in k_gemm.hip takes what this one does not (see conv_lds_fits).
+#include "xp_device.h"
+#include <type_traits>
+#include "xp_kernels.h"
+
+#include <cstdio>
+
+namespace xp {
+
+namespace {
+
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// calls f(integral_constant<int, I>) for I = B .. E-1
+template <int B, int E, typename F>
+XP_DEV void static_for(F&& f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
+
+// -1 where bit i of m is set, else 0
+XP_DEV int bit_mask(uint32_t m, int i) { return __builtin_amdgcn_sbfe((int)m, i, 1); }
+
+// 16 bytes per lane from the buffer to LDS at lds + 16 * lane (lds is the same
+// in all lanes); zeros where the offset is past the buffer's end
+XP_DEV void load_lds16(__amdgpu_buffer_rsrc_t r, bf16_t* lds, int voff, int soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, 0);
+}
+
+// waits until at most N of the wave's vector memory operations are outstanding
+template <int N>
+XP_DEV void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
+}
+// barrier of the workgroup that leaves loads to LDS in flight
+XP_DEV void wg_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// One workgroup per BM x BN output tile, WM x WN waves of 32x32x16 MFMA tiles.
+//
+// A reduction step is BK channels of one filter tap (RAG: BK consecutive
+// (tap, channel) positions, a tap per 16-byte chunk).  The A tile (BM pixels'
+// im2col rows) and the B tile (BN filters) of a step sit in LDS as BK-element
+// rows without padding; the 16-byte chunk c of row r is stored at position
+// c ^ swz(r), so that the rows one fragment read touches lie in different
+// banks.  A copy instruction writes 64 consecutive chunks; the swizzle is in
+// which chunk each lane asks for, and is the same for all of a lane's rows.
+// NS buffers: NS - 1 steps are in flight while one is multiplied, and a wave
+// waits only for its own copies of the step it needs (vmcnt), then for the
+// others' at the barrier.
+//
+// GM 0: same grid; 1: strided or unpadded forward (rows = Ho x Wo grid);
+// 2: strided data gradient.  There the rows are taken by the residue of their
+// row and column modulo the stride: the pixels of one residue class meet the
+// same taps, every tap that is multiplied reaches an output pixel, and a class
+// that no tap reaches (1x1 stride 2) is written without a product.
+template <int BM, int BN, int WM, int WN, int BK, int NS, bool RAG, int GM, bool DG>
+__global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int tiles_m) {
+  constexpr int NW = WM * WN;
+  constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
+  static_assert(WTM % 32 == 0 && (WTN == 32 || WTN == 64), "wave tile");
+  static_assert(BK == 32 || BK == 64, "step");
+  constexpr int CPR = BK / 8;    // chunks per row
+  constexpr int RPI = 64 / CPR;  // rows per copy instruction
+  constexpr int A_T = BM / RPI, B_T = BN / RPI;  // copy instructions per step
+  constexpr int A_I = (A_T + NW - 1) / NW, B_I = (B_T + NW - 1) / NW;  // per wave (some twice)
+  constexpr int LOADS = A_I + B_I;
+  constexpr int SZ = (BM + BN) * BK;
+  constexpr int SZ0 = SZ > NW * WTN * 32 ? SZ : NW * WTN * 32;  // the epilogue's strips: 16 rows at least
+  __shared__ __align__(16) bf16_t st0[SZ0];
+  __shared__ __align__(16) bf16_t st1[SZ];
+  __shared__ __align__(16) bf16_t st2[NS > 2 ? SZ : 8];
+  __shared__ __align__(16) bf16_t st3[NS > 3 ? SZ : 8];
+  __shared__ double sred[WM][2][BN];
+  static_assert(NS >= 2 && NS <= 4, "stages");
+  // separate arrays: the compiler then knows which copies a read can meet
+  auto stage = [&](auto I) __attribute__((always_inline)) -> bf16_t* {
+    constexpr int i = decltype(I)::value;
+    if constexpr (i == 0) return st0;
+    else if constexpr (i == 1) return st1;
+    else if constexpr (i == 2) return st2;
+    else return st3;
+  };
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int H = a.H, W = a.W, C = a.C, S = a.S;
+  const int Ho = GM ? a.Ho : H, Wo = GM ? a.Wo : W;
+  const int sd = GM ? a.stride : 1;
+  const int tlin = xcd_tile(blockIdx.x, gridDim.x);
+  const int ntn = gridDim.x / tiles_m;
+  const int tm = tlin / ntn, tn = tlin - tm * ntn;
+  const int n0 = tn * BN;
+
+  // the rows of this tile: pixel (img, h, w) of a gh x gw grid, output pixel
+  // (img, oy + h * od, ox + w * od), and the taps r0 + i * rs, s0 + j * rs
+  int m0 = tm * BM, gh = Ho, gw = Wo, oy = 0, ox = 0, od = 1;
+  int nR = a.R, nS = S, r0 = 0, s0 = 0, rs = 1;
+  if constexpr (GM == 2) {
+    od = rs = sd;
+    int t = tm;
+    for (int p = 0; p < sd * sd; ++p) {
+      oy = p / sd;
+      ox = p - oy * sd;
+      gh = (Ho - oy + sd - 1) / sd;
+      gw = (Wo - ox + sd - 1) / sd;
+      const int tiles = (a.nb * gh * gw + BM - 1) / BM;
+      if (t < tiles || p == sd * sd - 1) break;
+      t -= tiles;
+    }
+    m0 = t * BM;
+    r0 = (oy + a.pad) % sd;
+    s0 = (ox + a.padw) % sd;
+    nR = r0 < a.R ? (a.R - r0 + sd - 1) / sd : 0;
+    nS = s0 < S ? (S - s0 + sd - 1) / sd : 0;
+  }
+  const int M = a.nb * gh * gw;
+  const int K = a.R * S * C;
+
+  // resources: the input view, from (as many pixels before it as a tap's
+  // offset is made non-negative by), and the weights
+  const int back = GM == 2 ? (nR > 0 && nS > 0 ? (nR - 1) * W + nS - 1 : 0) : a.pad * W + a.padw;
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)((const bf16_t*)a.x - (size_t)back * a.ldx), (short)0,
+      (int)((((size_t)a.nb * H * W - 1 + back) * a.ldx + C) * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t wr =
+      __builtin_amdgcn_make_buffer_rsrc((void*)a.w, (short)0, (int)((size_t)a.N * K * 2), 0x00020000);
+
+  // the chunk of a row this lane copies, and per copy the row's byte offset
+  // and one bit per tap row (column) that does not land in the image
+  const int lrow = lane / CPR, lpos = lane % CPR;
+  const int kc = BK == 64 ? lpos ^ lrow : lpos ^ ((lrow >> 1) & 3);
+  uint32_t a_off[A_I], a_hb[A_I], a_wb[A_I], b_off[B_I];
+#pragma unroll
+  for (int i = 0; i < A_I; ++i) {
+    const int m = m0 + min(wave * A_I + i, A_T - 1) * RPI + lrow;
+    const int mm = m < M ? m : 0;
+    const int img = mm / (gh * gw), rem = mm - img * gh * gw, h = rem / gw, w = rem - h * gw;
+    uint32_t hb = ~0u, wb = ~0u;
+    int bh, bw;  // first source row and column (GM 2: last)
+    if constexpr (GM == 2) {
+      bh = h + (oy + a.pad - r0) / sd;
+      bw = w + (ox + a.padw - s0) / sd;
+      for (int r = 0; r < nR; ++r) hb ^= (uint32_t)((unsigned)(bh - r) < (unsigned)H) << r;
+      for (int q = 0; q < nS; ++q) wb ^= (uint32_t)((unsigned)(bw - q) < (unsigned)W) << q;
+    } else {
+      bh = h * sd;
+      bw = w * sd;
+      for (int r = 0; r < nR; ++r) hb ^= (uint32_t)((unsigned)(bh + r - a.pad) < (unsigned)H) << r;
+      for (int q = 0; q < nS; ++q) wb ^= (uint32_t)((unsigned)(bw + q - a.padw) < (unsigned)W) << q;
+    }
+    a_off[i] = (uint32_t)((((size_t)(img * H + bh) * W + bw) * a.ldx + (RAG ? 0 : kc * 8)) * 2);
+    a_hb[i] = m < M ? hb : ~0u;
+    a_wb[i] = wb;
+  }
+#pragma unroll
+  for (int i = 0; i < B_I; ++i) {
+    const int n = n0 + min(wave * B_I + i, B_T - 1) * RPI + lrow;
+    b_off[i] = n < a.N ? (uint32_t)(((size_t)n * K + (RAG ? 0 : kc * 8)) * 2) : ~0u;
+  }
+
+  // cursor of the next step to copy: tap (ci, cj), channel cc (RAG: of this
+  // lane's chunk), held at the last step
+  const int nk = RAG ? (nR * nS * C + BK - 1) / BK : nR * nS * (C / BK);
+  int ci = 0, cj = 0, cc = 0, copied = 0;
+  int av_r = 0, av_s = 0, av_c = 0;  // RAG: one step's advance
+  if constexpr (RAG) {
+    const int k0 = kc * 8, t0 = k0 / C;
+    cc = k0 - t0 * C;
+    ci = nS > 0 ? t0 / nS : 0;
+    cj = t0 - ci * nS;
+    const int t = BK / C;
+    av_c = BK - t * C;
+    av_r = nS > 0 ? t / nS : 0;
+    av_s = t - av_r * nS;
+  }
+  auto copy = [&](auto I) __attribute__((always_inline)) {
+    bf16_t* sa = stage(I);
+    bf16_t* sb = stage(I) + BM * BK;
+    const int pix = GM == 2 ? (nR - 1 - ci) * W + (nS - 1 - cj) : ci * W + cj;
+    const int ka = (pix * a.ldx + cc) * 2;
+    const int kb = (((r0 + ci * rs) * S + s0 + cj * rs) * C + cc) * 2;
+    const int past = RAG ? (ci < nR ? 0 : -1) : 0;
+#pragma unroll
+    for (int i = 0; i < A_I; ++i) {
+      const int bad = bit_mask(a_hb[i], ci) | bit_mask(a_wb[i], cj);
+      if constexpr (RAG) load_lds16(xr, sa + min(wave * A_I + i, A_T - 1) * 512, (int)(a_off[i] + (uint32_t)ka) | bad, 0);
+      else load_lds16(xr, sa + min(wave * A_I + i, A_T - 1) * 512, (int)a_off[i] | bad, ka);
+    }
+#pragma unroll
+    for (int i = 0; i < B_I; ++i) {
+      if constexpr (RAG)
+        load_lds16(wr, sb + min(wave * B_I + i, B_T - 1) * 512, b_off[i] == ~0u ? -1 : (int)(b_off[i] + (uint32_t)kb) | past, 0);
+      else load_lds16(wr, sb + min(wave * B_I + i, B_T - 1) * 512, (int)b_off[i], kb);
+    }
+    const bool adv = ++copied < nk;
+    if constexpr (RAG) {
+      if (adv) {
+        cc += av_c;
+        cj += av_s;
+        ci += av_r;
+        if (cc >= C) {
+          cc -= C;
+          ++cj;
+        }
+        if (cj >= nS) {
+          cj -= nS;
+          ++ci;
+        }
+      }
+    } else {
+      const bool wc = adv && cc + BK >= C;
+      const bool wq = wc && cj + 1 == nS;
+      cc = wc ? 0 : cc + (adv ? BK : 0);
+      cj = wq ? 0 : cj + (int)wc;
+      ci += (int)wq;
+    }
+  };
+
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+
+  // fragment of a 32-row, 16-deep slice: lane l holds row l % 32, elements 8 (l / 32) .. + 8
+  const int frow = lane & 31, fsw = BK == 64 ? frow & 7 : (frow >> 1) & 3;
+  auto multiply = [&](auto I) __attribute__((always_inline)) {
+    const bf16_t* sa = stage(I) + (wm * WTM + frow) * BK;
+    const bf16_t* sb = stage(I) + (BM + wn * WTN + frow) * BK;
+#pragma unroll
+    for (int kk = 0; kk < BK / 16; ++kk) {
+      const int p = ((kk * 2 + (lane >> 5)) ^ fsw) * 8;
+      bf16x8_t af[TM], bf[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const bf16x8_t*>(sa + i * 32 * BK + p);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bf[j] = *reinterpret_cast<const bf16x8_t*>(sb + j * 32 * BK + p);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
+    }
+  };
+
+  if (nk > 0) {
+    static_for<0, NS - 1>([&](auto I) __attribute__((always_inline)) { copy(I); });
+    int k = 0;
+    while (true) {
+      bool done = false;
+      static_for<0, NS>([&](auto I) __attribute__((always_inline)) {
+        constexpr int i = decltype(I)::value;
+        if (!done) {
+          // this wave's copies of step k have landed; past the barrier so have
+          // the others', and all waves have read the buffer that is refilled
+          wait_vm<(NS - 2) * LOADS>();
+          wg_barrier();
+          copy(std::integral_constant<int, (i + NS - 1) % NS>{});
+          __builtin_amdgcn_sched_barrier(0);  // (left to itself the compiler issues the copies last)
+          multiply(I);
+          done = ++k == nk;
+        }
+      });
+      if (done) break;
+    }
+    wait_vm<0>();
+  }
+  wg_barrier();
+
+  // ------------------------------------------------------------- epilogue
+  // Each wave finishes its tile in strips of rows through its own part of LDS
+  // (no barrier), with 16-byte global accesses.  Column sums (batch-norm
+  // statistics of the stored values, or backward partials) are fp64, added in
+  // registers over the wave's rows and then across lanes and waves in a fixed
+  // order.
+  constexpr int CW = WTN / 8;                         // 8-column chunks per strip row
+  constexpr int SR = SZ0 >= NW * WTN * 64 ? 32 : 16;  // strip rows
+  constexpr int PASS = SR * CW / 64;                  // chunks per lane and strip
+  constexpr int LPR = 64 / CW;                        // rows per pass
+  constexpr int STRIPS = TM * 32 / SR;
+  const int ch = lane % CW, n = n0 + wn * WTN + ch * 8;
+  const bool live_n = n < a.N;
+  bf16_t* y = (bf16_t*)a.y;
+  // output pixel of the lane's chunk of pass p in strip t, or -1
+  auto out_row = [&](int t, int p) __attribute__((always_inline)) -> int {
+    const int m = m0 + wm * WTM + t * SR + p * LPR + lane / CW;
+    if (!live_n || m >= M) return -1;
+    if constexpr (GM == 2) {
+      const int img = m / (gh * gw), rem = m - img * gh * gw, h = rem / gw, w = rem - h * gw;
+      return (img * Ho + oy + h * od) * Wo + ox + w * od;
+    }
+    return m;
+  };
+  if constexpr (!DG) {
+    // Forward: a lane holds a column of each 32x32 result (16 rows of it), so
+    // bias, ReLU, the rounding and the column sums are taken there, and the
+    // strip goes through LDS as bf16.
+    bf16_t* ot = st0 + wave * (SR * WTN);
+    float bias[TN];
+    double s0[TN], s1[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int col = n0 + wn * WTN + j * 32 + (lane & 31);
+      bias[j] = a.bias && col < a.N ? a.bias[col] : 0.f;
+      s0[j] = s1[j] = 0.0;
+    }
+    const int rows = M - m0 - wm * WTM;  // rows of this wave's tile that exist
+    const bool cut = a.bias && rows < WTM;
+#pragma unroll
+    for (int t = 0; t < STRIPS; ++t) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < SR / 2; r += 2) {
+          // register r of the 32x32 result: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
+          const int row = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          const int q = (t * SR % 32) / 2 + r;
+          float f0 = acc[t * SR / 32][j][q] + bias[j], f1 = acc[t * SR / 32][j][q + 1] + bias[j];
+          if (a.relu) {
+            f0 = f0 > 0.f ? f0 : 0.f;
+            f1 = f1 > 0.f ? f1 : 0.f;
+          }
+          if (cut) {  // rows past the last hold the bias alone
+            f0 = t * SR + row < rows ? f0 : 0.f;
+            f1 = t * SR + row + 1 < rows ? f1 : 0.f;
+          }
+          const uint32_t pr = f32x2_to_bf16x2(f0, f1);
+          int col = j * 32 + (lane & 31);
+          if constexpr (WTN == 64) col ^= 32 * (lane >> 5);  // (row & 4): the halves' rows in different banks
+          ot[row * WTN + col] = (bf16_t)pr;
+          ot[(row + 1) * WTN + col] = (bf16_t)(pr >> 16);
+          if (a.stat_part) {
+            const double v0 = (double)__uint_as_float(pr << 16), v1 = (double)__uint_as_float(pr & 0xffff0000u);
+            s0[j] += v0;
+            s1[j] += v0 * v0;
+            s0[j] += v1;
+            s1[j] += v1 * v1;
+          }
+        }
+#pragma unroll
+      for (int p = 0; p < PASS; ++p) {
+        const int row = p * LPR + lane / CW;
+        int col = ch * 8;
+        if constexpr (WTN == 64) col ^= (row & 4) << 3;
+        const u32x4_t pr = *reinterpret_cast<const u32x4_t*>(ot + row * WTN + col);
+        const int m = out_row(t, p);
+        if (m >= 0) *reinterpret_cast<u32x4_t*>(y + (size_t)m * a.ldy + n) = pr;
+      }
+    }
+    if (!a.stat_part) return;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      s0[j] += __shfl_xor(s0[j], 32, 64);
+      s1[j] += __shfl_xor(s1[j], 32, 64);
+      if (lane < 32) {
+        sred[wm][0][wn * WTN + j * 32 + lane] = s0[j];
+        sred[wm][1][wn * WTN + j * 32 + lane] = s1[j];
+      }
+    }
+  } else {
+    // Data gradient: mask, earlier contribution and batch-norm input come in
+    // 16-byte chunks, so the fp32 strip goes through LDS and a lane finishes
+    // chunks of one chunk column.
+    float* ot = reinterpret_cast<float*>(st0) + wave * (SR * WTN);
+    const bf16_t* mask = (const bf16_t*)a.mask;
+    const bf16_t* z = nullptr;  // input of the batch norm whose output gradient these columns are
+    const double *mean = nullptr, *rstd = nullptr;
+    int ldz = 0;
+    if (a.bn_part && live_n) {
+#pragma unroll
+      for (int q = 0; q < CONV_BN_SEGS; ++q)
+        if (q < a.bn_nseg && n >= a.bn_c0[q] && n < a.bn_c1[q] && a.bn_z[q]) {
+          z = (const bf16_t*)a.bn_z[q] + (n - a.bn_c0[q]);
+          mean = a.bn_mean[q] + (n - a.bn_c0[q]);
+          rstd = a.bn_rstd[q] + (n - a.bn_c0[q]);
+          ldz = a.ld_bnz[q];
+        }
+    }
+    double v[16];  // column sums: of g, then of g z
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[e] = 0.0;
+#pragma unroll
+    for (int t = 0; t < STRIPS; ++t) {
+      u32x4_t c_mask[PASS], c_old[PASS], c_z[PASS];
+      int c_m[PASS];
+#pragma unroll
+      for (int p = 0; p < PASS; ++p) {
+        const int m = c_m[p] = out_row(t, p);
+        c_mask[p] = c_old[p] = c_z[p] = (u32x4_t){0u, 0u, 0u, 0u};
+        if (m >= 0) {
+          if (mask) c_mask[p] = *reinterpret_cast<const u32x4_t*>(mask + (size_t)m * a.ldm + n);
+          if (a.accumulate) c_old[p] = *reinterpret_cast<const u32x4_t*>(y + (size_t)m * a.ldy + n);
+          if (z) c_z[p] = *reinterpret_cast<const u32x4_t*>(z + (size_t)m * ldz);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < SR / 2; ++r) {
+          const int row = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          int col = j * 32 + (lane & 31);
+          if constexpr (WTN == 64) col ^= 32 * (lane >> 5);
+          ot[row * WTN + col] = acc[t * SR / 32][j][(t * SR % 32) / 2 + r];
+        }
+#pragma unroll
+      for (int p = 0; p < PASS; ++p) {
+        const int row = p * LPR + lane / CW;
+        int col = ch * 8;
+        if constexpr (WTN == 64) col ^= (row & 4) << 3;
+        const f32x4_t lo = *reinterpret_cast<const f32x4_t*>(ot + row * WTN + col);
+        const f32x4_t hi = *reinterpret_cast<const f32x4_t*>(ot + row * WTN + col + 4);
+        float f[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          // one fp32 rounding of acc + y equals the rounding of their exact
+          // double sum (53 >= 2 * 24 + 2)
+          float x = e < 4 ? lo[e] : hi[e - 4];
+          const uint32_t mw = c_mask[p][e >> 1], ow = c_old[p][e >> 1];
+          if (mask && !(__uint_as_float((e & 1) ? (mw & 0xffff0000u) : (mw << 16)) > 0.0f)) x = 0.f;
+          if (a.accumulate) x += __uint_as_float((e & 1) ? (ow & 0xffff0000u) : (ow << 16));
+          f[e] = x;
+        }
+        u32x4_t pr;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) pr[q] = f32x2_to_bf16x2(f[2 * q], f[2 * q + 1]);
+        const int m = c_m[p];
+        if (m >= 0) {
+          *reinterpret_cast<u32x4_t*>(y + (size_t)m * a.ldy + n) = pr;
+          if (a.bn_part) {
+            // the stored gradient, as what reads it sees it
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const uint32_t w = pr[e >> 1], zw = c_z[p][e >> 1];
+              const double g = (double)__uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
+              v[e] += g;
+              v[8 + e] += g * (double)__uint_as_float((e & 1) ? (zw & 0xffff0000u) : (zw << 16));
+            }
+          }
+        }
+      }
+    }
+    if (!a.bn_part) return;
+    // sum of g (z - mean) rstd; the products are exact in fp64, and a bf16 z
+    // bounds what the difference can cancel (mean / deviation below 2^9)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[8 + e] = z ? (v[8 + e] - mean[e] * v[e]) * rstd[e] : 0.0;
+    // add across the lanes of one chunk column, halving the values a lane keeps
+    int idx = 0, nv = 16;
+#pragma unroll
+    for (int st = 32; st >= CW; st >>= 1) {
+      const bool hi = (lane & st) != 0;
+      nv >>= 1;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (e < nv) {
+          const double send = hi ? v[e] : v[e + nv], keep = hi ? v[e + nv] : v[e];
+          v[e] = keep + __shfl_xor(send, st, 64);
+        }
+      idx += hi ? nv : 0;
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      if (e < nv) sred[wm][(idx + e) >> 3][wn * WTN + ch * 8 + ((idx + e) & 7)] = v[e];
+  }
+  __syncthreads();
+  double* part = DG ? a.bn_part : a.stat_part;
+  for (int q = tid; q < 2 * BN; q += NW * 64) {
+    const int which = q / BN, col = q - which * BN;
+    if (n0 + col >= a.N) continue;
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < WM; ++w) s += sred[w][which][col];
+    part[((size_t)(n0 + col) * 2 + which) * tiles_m + tm] = s;
+  }
+}
+
+template <int BM, int BN, int WM, int WN, int BK, int NS, bool RAG, int GM, bool DG = GM == 2>
+hipError_t go(const ConvArgs& a, hipStream_t s, int* row_tiles) {
+  int tiles = 0;
+  if (GM == 2) {
+    for (int p = 0; p < a.stride * a.stride; ++p)
+      tiles += (a.nb * ((a.Ho - p / a.stride + a.stride - 1) / a.stride) *
+                    ((a.Wo - p % a.stride + a.stride - 1) / a.stride) + BM - 1) / BM;
+  } else {
+    tiles = (a.nb * (GM ? a.Ho * a.Wo : a.H * a.W) + BM - 1) / BM;
+  }
+  if (row_tiles) *row_tiles = tiles;
+  const double rows = GM == 1 ? (double)a.Ho * a.Wo : (double)a.H * a.W;  // (GM 2: each dy pixel meets each tap)
+  const double flops = 2.0 * a.nb * rows * a.N * a.R * a.S * a.C;
+  static const struct Name {
+    char s[72];
+    Name() {
+      snprintf(s, sizeof s, "k_conv_gemm_lds<%d,%d,%d,%d,%d,%d,%s,%d,%s>", BM, BN, WM, WN, BK, NS,
+               RAG ? "true" : "false", GM, DG ? "true" : "false");
+    }
+  } name;
+  XP_LAUNCH(name.s, flops, (k_conv_gemm_lds<BM, BN, WM, WN, BK, NS, RAG, GM, DG>), dim3(tiles * ((a.N + BN - 1) / BN)),
+            dim3(WM * WN * 64), 0, s, a, tiles);
+  return hipGetLastError();
+}
+
+bool chunks16(const void* p, int ld) { return (reinterpret_cast<uintptr_t>(p) % 16) == 0 && ld % 8 == 0; }
+
+int64_t tiles(int64_t rows, int bm, int cols, int bn) { return ((rows + bm - 1) / bm) * ((cols + bn - 1) / bn); }
+
+// Tile by size, from a sweep of the stages' shapes (us per launch, MI355X):
+//  - up to 32 columns 128x32, up to 64 128x64 (3x3 64->64 at 56x56x100: 46.5,
+//    64x64 tiles 52.5), 65..96 96x96 (3x3 64->96 at 35x35x32: 14.6; 64x128
+//    15.5, 128x64 16.0);
+//  - wider: 128x128 on eight waves while it gives 400 tiles (1x1 256->1024 at
+//    14x14x100: 27.4, 64x128 30.6; below that, 3x3 256->256 there, 306 tiles:
+//    41.3 against 38.1), then 64x128, then 64x64 (3x3 512->512 at 7x7x100:
+//    43.8 / 39.5); 64 columns where 128 would pad by more than a quarter
+//    (1x1 256->176: 15.4 against 16.8);
+//  - a data gradient over very many rows and 256 columns or a multiple, whose
+//    time is its epilogue's four tensors, takes rows of 256 columns in one
+//    workgroup (1x1 64->256 at 56x56x100: 131, 128x128 150).
+// Two buffers: a third or fourth lost more workgroups per CU than it hid.
+template <bool RAG, int GM, bool DG>
+hipError_t pick_tile(const ConvArgs& a, int64_t rows, hipStream_t s, int* row_tiles) {
+  if (a.N <= 32) return go<128, 32, 4, 1, 64, 2, RAG, GM, DG>(a, s, row_tiles);
+  const int64_t pad64 = (a.N + 63) / 64 * 64, pad128 = (a.N + 127) / 128 * 128;
+  if (a.N > 96 && 4 * pad128 <= 5 * pad64) {
+    if constexpr (DG && GM == 0)
+      if (a.N % 256 == 0 && tiles(rows, 256, a.N, 256) >= 1024)
+        return go<256, 256, 2, 4, 64, 2, RAG, GM, DG>(a, s, row_tiles);
+    if (tiles(rows, 128, a.N, 128) >= 400) return go<128, 128, 4, 2, 64, 2, RAG, GM, DG>(a, s, row_tiles);
+    if (tiles(rows, 64, a.N, 128) >= 400) return go<64, 128, 2, 2, 64, 2, RAG, GM, DG>(a, s, row_tiles);
+  } else if (tiles(rows, 128, a.N, 64) >= 512) {
+    if (a.N > 64 && a.N <= 96) return go<96, 96, 1, 3, 32, 3, RAG, GM, DG>(a, s, row_tiles);
+    return go<128, 64, 4, 2, 64, 2, RAG, GM, DG>(a, s, row_tiles);
+  }
+  return go<64, 64, 2, 2, 64, 2, RAG, GM, DG>(a, s, row_tiles);
+}
+
+template <int GM, bool DG>
+hipError_t pick_step(const ConvArgs& a, int64_t rows, hipStream_t s, int* row_tiles) {
+  // (the 96x96 tile steps by 32 channels)
+  const int bk = a.N > 64 && a.N <= 96 && tiles(rows, 128, a.N, 64) >= 512 ? 32 : 64;
+  return a.C % bk == 0 ? pick_tile<false, GM, DG>(a, rows, s, row_tiles)
+                       : pick_tile<true, GM, DG>(a, rows, s, row_tiles);
+}
+
+}  // namespace
+
+bool launch_conv_lds(const ConvArgs& a, hipStream_t s, int* row_tiles, hipError_t* e) {
+  const int stride = a.stride < 1 ? 1 : a.stride;
+  const bool dg = a.tr || a.mask || a.accumulate || a.bn_part;
+  const bool grid = a.Ho > 0;
+  const int64_t rows = (int64_t)a.nb * (grid ? a.Ho * a.Wo : a.H * a.W);
+  // what the kernel is written for: 16-byte chunks of every view, byte offsets
+  // of 31 bits from the first tap on, whole chunks of columns per batch norm,
+  // bias and ReLU forward, mask and accumulation backward
+  bool fits = a.C % 8 == 0 && a.N % 8 == 0 && chunks16(a.x, a.ldx) && chunks16(a.y, a.ldy) && chunks16(a.w, 8) &&
+              (!a.mask || chunks16(a.mask, a.ldm)) && !(dg && (a.bias || a.relu || a.stat_part)) &&
+              (grid || (!a.tr && stride == 1));
+  const int64_t pixels = (int64_t)a.nb * a.H * a.W + (int64_t)a.R * a.W + a.S;
+  fits = fits && pixels * a.ldx * 2 < ((int64_t)1 << 31) && (int64_t)a.N * a.R * a.S * a.C * 2 < ((int64_t)1 << 31);
+  if (a.bn_part)
+    for (int k = 0; k < a.bn_nseg; ++k)
+      fits = fits && a.bn_c0[k] % 8 == 0 && a.bn_c1[k] % 8 == 0 && (!a.bn_z[k] || chunks16(a.bn_z[k], a.ld_bnz[k]));
+  // fewer tiles than CUs: the general kernel's smaller tiles give more
+  // (3x3 512->512 at 4x4x32, 64 tiles: 34.8 against 20.7 us; 3x3 256->256 at
+  // 8x8x32, 128 tiles: 13.8 against 12.8; 3x3 128->128 at 16x16x32, 256 tiles:
+  // 9.7 against 11.5)
+  fits = fits && tiles(rows, 64, a.N, a.N <= 32 ? 32 : 64) >= 192;
+  // the residue classes' last tiles stay within conv_max_row_tiles
+  fits = fits && (!a.tr || rows >= 256);
+  if (!fits) return false;
+  ConvArgs b = a;
+  b.stride = stride;
+  if (a.tr) *e = pick_step<2, true>(b, rows, s, row_tiles);
+  else if (grid && dg) return false;
+  else if (grid) *e = pick_step<1, false>(b, rows, s, row_tiles);
+  else if (dg) *e = pick_step<0, true>(b, rows, s, row_tiles);
+  else *e = pick_step<0, false>(b, rows, s, row_tiles);
+  return true;
+}
+
+}  // namespace xp

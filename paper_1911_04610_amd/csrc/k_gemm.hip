@@ -1467,19 +1467,6 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
     // strided or unpadded layers (ResNet-101 stem, first blocks, projections;
     // Inception-V3 stem and grid reductions): general tiles
     if constexpr (sizeof(T) == 2) {
-      // large grids (first stages at 224 x 224 over micro-batch 100): 128-row
-      // tiles, or one 96-column tile for 64 < N <= 96; 10-33% faster there
-      const size_t rows = (size_t)a.nb * a.Ho * a.Wo;
-      if (!flat && !narrow && rows >= 65536) {
-        if (a.tr) {
-          if (a.N <= 64) return conv_go<T, 128, 64, 2, 2, 2, 2, 2>(a, flat, s, gr);
-          if (a.N <= 96) return conv_go<T, 64, 96, 2, 2, 1, 2, 2>(a, flat, s, gr);
-          return conv_go<T, 128, 128, 2, 4, 2, 2, 2>(a, flat, s, gr);
-        }
-        if (a.N <= 64) return conv_go<T, 128, 64, 2, 2, 2, 2, 1>(a, flat, s, gr);
-        if (a.N <= 96) return conv_go<T, 64, 96, 2, 2, 1, 2, 1>(a, flat, s, gr);
-        return conv_go<T, 128, 128, 2, 4, 2, 2, 1>(a, flat, s, gr);
-      }
       if (a.tr) {
         if (narrow) return conv_go<T, 64, 32, 2, 2, 1, 2, 2>(a, flat, s, gr);
         return conv_go<T, 64, 64, 2, 2, 2, 2, 2>(a, flat, s, gr);
@@ -1496,8 +1483,8 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
     }
   }
   if constexpr (sizeof(T) == 2) {
-    // From a sweep of the stage shapes on MI355X (tile, stage depth KS,
-    // register prefetch depth PF)
+    // What launch_conv_lds leaves: few tiles, odd channel counts or views.
+    // From a sweep on MI355X (tile, stage depth KS, register prefetch depth PF)
     const int taps = a.R * a.S;
     const int ks = flat ? 1 : pick_ks_bf16(a.C, taps);
     // KS counts 32-deep slices for the 16x16 MFMA tiles and 16-deep slices
@@ -1507,28 +1494,7 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
       if (ks == 2) return conv_go<T, 32, 32, 2, 2, 2, 3>(a, flat, s, gr);
       return conv_go<T, 64, 32, 2, 2, 1, 2>(a, flat, s, gr);
     }
-    // large images (ResNet-101 at 224 x 224 over micro-batch 100: 78 400 to
-    // 313 600 rows): 128-row tiles, 128 columns on eight waves where N allows;
-    // 4-17% faster there than the 32- and 64-row tiles
-    if (!flat && M >= 65536 && (a.N <= 64 || a.N >= 128)) {
-      if (a.N <= 64) return conv_go<T, 128, 64, 2, 2, 2, 2>(a, flat, s, gr);
-      return conv_go<T, 128, 128, 2, 4, 2, 2>(a, flat, s, gr);
-    }
-    // one 96-column tile reads the input once and wastes no MFMA columns
-    if (!flat && taps > 1 && taps < 25 && a.N > 64 && a.N <= 96)
-      return conv_go<T, 64, 96, 2, 2, 1, 2>(a, flat, s, gr);
     if (ks == 1) return conv_go<T, 64, 64, 2, 2, 2, 2>(a, flat, s, gr);
-    if (!flat && taps == 1 && a.N > 96 && M >= 16384) {
-      // wide 1x1 (merged siblings) over many rows: 64-row tiles, the column
-      // tile that pads N least
-      if ((a.N + 95) / 96 * 96 <= (a.N + 63) / 64 * 64)
-        return conv_go<T, 64, 96, 2, 2, 1, 2>(a, flat, s, gr);
-      return conv_go<T, 64, 64, 2, 2, 2, 2>(a, flat, s, gr);
-    }
-    if (taps >= 25 && a.N > 48) {
-      if (ks == 4) return conv_go<T, 64, 64, 2, 2, 8, 2>(a, flat, s, gr);
-      return conv_go<T, 64, 64, 2, 2, 4, 2>(a, flat, s, gr);
-    }
     if (ks == 4) return conv_go<T, 32, 64, 2, 2, 4, 2>(a, flat, s, gr);
     return conv_go<T, 32, 64, 2, 2, 2, 2>(a, flat, s, gr);
   } else {
@@ -1540,6 +1506,8 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
 hipError_t launch_conv_gemm(int dtype, const ConvArgs& a, hipStream_t s, int* grid_rows) {
   if (grid_rows) *grid_rows = 0;
   if (a.nb * a.H * a.W <= 0 || a.N <= 0) return hipSuccess;
+  hipError_t e = hipSuccess;
+  if (dtype == DT_BF16 && launch_conv_lds(a, s, grid_rows, &e)) return e;
   return dtype == DT_BF16 ? conv_dispatch<bf16_t>(a, s, grid_rows)
                           : conv_dispatch<float>(a, s, grid_rows);
 }

@@ -151,6 +151,10 @@ struct WgradArgs {
 // Work plan of one GEMM launch (tile shape picked on the host).
 // grid_rows (optional) receives the number of row tiles of the launch
 hipError_t launch_conv_gemm(int dtype, const ConvArgs& a, hipStream_t s, int* grid_rows = nullptr);
+// the bf16 kernel that copies its operands straight into LDS (k_conv.hip):
+// false when the call is not one it is written for or has too few tiles, and
+// then nothing is launched; else the launch's status in *e
+bool launch_conv_lds(const ConvArgs& a, hipStream_t s, int* row_tiles, hipError_t* e);
 // row tiles the forward-type GEMM uses for M rows (upper bound over tile choices)
 int conv_max_row_tiles(int M);
 size_t wgrad_part_bytes(int dtype, int N, int K, int splits);

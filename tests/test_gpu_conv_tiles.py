@@ -1,0 +1,91 @@
+"""The tiles and gathers of the bf16 convolution that copies its operands
+straight into LDS (csrc/k_conv.hip), each through a small stage whose sizes
+reach it with a ragged last tile, against the oracle's bf16 model (and the exact
+one where no ReLU is present) at the bf16 bar, 2e-2.
+
+A case is picked by rows (micro-batch x H x W), output channels and input
+channels: channels that are no multiple of the 64-channel step take a filter
+tap per 16-byte chunk; strided data gradients take their rows by residue class,
+also classes that no tap reaches (1 x 1, stride 2)."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1911_04610_amd as xp
+import workloads as wl
+from conftest import rel_l2
+from gpu_harness import run_stage
+from test_gpu_layers import _errs, bn, conv
+
+pytestmark = pytest.mark.gpu
+
+
+def relu(x):
+    return dict(kind="relu", inputs=[x])
+
+
+CASES = {
+    # name: (layers, per-sample input shape, micro-batch)
+    "64x64": ([conv(-1, 64, 256, 3)], (29, 27, 64), 4),
+    "64x64_chunk_taps": ([conv(-1, 72, 256, 3)], (29, 27, 72), 4),
+    "64x64_8_channels_1x7": ([conv(-1, 8, 256, 1, kw=7)], (29, 27, 8), 4),
+    "64x128": ([conv(-1, 64, 256, 1)], (57, 57, 64), 4),
+    "128x128_chunk_taps": ([conv(-1, 40, 512, 1)], (57, 57, 40), 4),
+    "128x64_bias_relu": ([conv(-1, 48, 64, 3, True), relu(0)], (129, 128, 48), 4),
+    "96x96": ([conv(-1, 32, 96, 3), bn(0, 96)], (91, 91, 32), 4),
+    "96x96_chunk_taps": ([conv(-1, 24, 88, 5)], (91, 91, 24), 4),
+    "128x32": ([conv(-1, 64, 24, 3, True)], (57, 57, 64), 4),
+    "strided": ([conv(-1, 64, 256, 3, stride=2)], (57, 55, 64), 4),
+    "strided_1x1": ([conv(-1, 256, 512, 1, stride=2)], (81, 80, 256), 4),
+    "strided_7x7_chunk_taps": ([conv(-1, 40, 256, 7, stride=2)], (57, 56, 40), 4),
+    "unpadded": ([conv(-1, 64, 256, 5, pad="valid")], (33, 32, 64), 4),
+    # data gradients with mask, accumulation and batch-norm backward partials
+    "bn_partials": ([conv(-1, 64, 256, 1), bn(0, 256), relu(1), conv(2, 256, 64, 3), bn(3, 64), conv(2, 256, 72, 1),
+                     dict(kind="concat", inputs=[4, 5])], (57, 57, 64), 4),
+    "bn_partials_96": ([conv(-1, 32, 88, 1), bn(0, 88), relu(1), conv(2, 88, 32, 3)], (91, 91, 32), 4),
+    "bn_partials_strided": ([conv(-1, 32, 128, 1), bn(0, 128), relu(1), conv(2, 128, 64, 3, stride=2)],
+                            (65, 63, 32), 4),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_conv_tiles_match_oracle(name):
+    layers, shape, mb = CASES[name]
+    w = wl.StageWorkload(name, layers, mb, 1, shape, 1, 0, 0, 0, minibatches=1, seed=131)
+    inp = wl.stage_inputs(w, act_dtype="bf16")
+    gpu, _ = run_stage(w, inp, xp.BF16, xp.Hyper(), 0, 0, minibatches=1)
+    modes = ["bf16"] if any(L["kind"] == "relu" for L in layers) else ["bf16", "f64"]
+    for mode in modes:
+        ref = oracle.train_stage(oracle.Stage(layers, mode), inp.params, inp.m, inp.v, inp.xs, 0, 0,
+                                 oracle.Hyper(), labels=inp.labels, dys=inp.dys)[0]
+        e = _errs(gpu[0], ref)
+        worst = max(e, key=e.get)
+        print(f"{name} vs oracle-{mode}: worst {worst} = {e[worst]:.2e}")
+        bad = {k: v for k, v in e.items() if not v <= 2e-2}
+        assert not bad, f"vs oracle-{mode}: " + ", ".join(f"{k}={v:.2e}" for k, v in bad.items())
+
+
+def test_wide_data_gradient_tile():
+    """256 x 256 tiles (rows of 256 columns in one workgroup): the masked data
+    gradient of a 1 x 1 convolution over 262 160 rows, against fp64 products.
+    Bound per value: half a unit in bf16's last place (8 significant bits: 2^-8 of
+    the value) of a sum that 16 fp32 additions left within 16 x 2^-24 of the sum
+    of its terms' magnitudes."""
+    import torch
+    mb, hw, cin, cout = 5, (214, 245), 256, 16
+    st = xp.Stage([relu(-1), conv(0, cin, cout, 1)], mb, 1, hw + (cin,), xp.BF16)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    W = (torch.randn(cout, cin, generator=g, device="cuda") / 16).to(torch.bfloat16).float()
+    st.W[:cout * cin] = W.reshape(-1)
+    for d in (xp.FWD, xp.BWD):
+        st.xpipe_predict_weights(d, 0, xp.Hyper(), 0)
+    x = torch.randn(mb, *hw, cin, generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randn(mb, *hw, cout, generator=g, device="cuda").to(torch.bfloat16)
+    dx = torch.empty_like(x)
+    st.xpipe_stage_bwd(x, dy, None, dx)
+    ref = (dy.double().reshape(-1, cout) @ W.double()) * (x.reshape(-1, cin) > 0)
+    summed = 16 * 2.0 ** -24 * (dy.double().abs().reshape(-1, cout) @ W.double().abs())
+    d = (dx.reshape(-1, cin).double() - ref).abs()
+    assert bool((d <= 2.0 ** -8 * (ref.abs() + summed) + summed).all()), float(d.max())
+    assert rel_l2(np.asarray(st.get_tensors(st.grad)[0]),
+                  (dy.double().reshape(-1, cout).t() @ x.double().relu().reshape(-1, cin)).cpu().numpy().ravel()) <= 2e-3
