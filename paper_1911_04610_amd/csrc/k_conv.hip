@@ -33,15 +33,14 @@ XP_DEV void load_lds16(__amdgpu_buffer_rsrc_t r, bf16_t* lds, int voff, int soff
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, 0);
 }
 
-// waits until at most N of the wave's vector memory operations are outstanding
+// Waits until at most N of the wave's vector memory operations are outstanding
+// and its LDS reads have returned, then for the workgroup (a barrier that
+// leaves later loads to LDS in flight).
 template <int N>
-XP_DEV void wait_vm() {
+XP_DEV void wait_step() {
   static_assert(N >= 0 && N < 64, "vmcnt");
-  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
-}
-// barrier of the workgroup that leaves loads to LDS in flight
-XP_DEV void wg_barrier() {
   asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
@@ -64,9 +63,14 @@ XP_DEV void wg_barrier() {
 // row and column modulo the stride: the pixels of one residue class meet the
 // same taps, every tap that is multiplied reaches an output pixel, and a class
 // that no tap reaches (1x1 stride 2) is written without a product.
-template <int BM, int BN, int WM, int WN, int BK, int NS, bool RAG, int GM, bool DG>
-__global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int tiles_m) {
-  constexpr int NW = WM * WN;
+//
+// FEW (few tiles, a long reduction): a 32 x 32 tile whose four waves hold 16 x 16
+// results each (16x16x32 MFMA), with more steps in flight; one wave finishes
+// the tile.  Every element is still one chain of sums in channel order.
+template <int BM, int BN, int WM, int WN, int BK, int NS, bool RAG, int GM, bool DG, bool FEW, int UF>
+__global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int tiles_m) {
+  constexpr int NW = FEW ? 4 : WM * WN;
+  static_assert(!FEW || (WM * WN == 1 && BM == 32 && BN == 32 && BK == 64), "four 16 x 16 waves");
   constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
   static_assert(WTM % 32 == 0 && (WTN == 32 || WTN == 64), "wave tile");
   static_assert(BK == 32 || BK == 64, "step");
@@ -76,24 +80,34 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int 
   constexpr int A_I = (A_T + NW - 1) / NW, B_I = (B_T + NW - 1) / NW;  // per wave (some twice)
   constexpr int LOADS = A_I + B_I;
   constexpr int SZ = (BM + BN) * BK;
-  constexpr int SZ0 = SZ > NW * WTN * 32 ? SZ : NW * WTN * 32;  // the epilogue's strips: 16 rows at least
+  constexpr int SZ0 = SZ > WM * WN * WTN * 32 ? SZ : WM * WN * WTN * 32;  // the epilogue's strips: 16 rows at least
   __shared__ __align__(16) bf16_t st0[SZ0];
   __shared__ __align__(16) bf16_t st1[SZ];
   __shared__ __align__(16) bf16_t st2[NS > 2 ? SZ : 8];
   __shared__ __align__(16) bf16_t st3[NS > 3 ? SZ : 8];
+  __shared__ __align__(16) bf16_t st4[NS > 4 ? SZ : 8];
+  __shared__ __align__(16) bf16_t st5[NS > 5 ? SZ : 8];
+  __shared__ __align__(16) bf16_t st6[NS > 6 ? SZ : 8];
+  __shared__ __align__(16) bf16_t st7[NS > 7 ? SZ : 8];
   __shared__ double sred[WM][2][BN];
-  static_assert(NS >= 2 && NS <= 4, "stages");
+  static_assert(NS >= 2 && NS <= 8, "stages");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool finish = !FEW || wave == 0;  // the waves of the epilogue
   // separate arrays: the compiler then knows which copies a read can meet
   auto stage = [&](auto I) __attribute__((always_inline)) -> bf16_t* {
     constexpr int i = decltype(I)::value;
     if constexpr (i == 0) return st0;
     else if constexpr (i == 1) return st1;
     else if constexpr (i == 2) return st2;
-    else return st3;
+    else if constexpr (i == 3) return st3;
+    else if constexpr (i == 4) return st4;
+    else if constexpr (i == 5) return st5;
+    else if constexpr (i == 6) return st6;
+    else return st7;
   };
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
+  const int wm = FEW ? 0 : wave / WN, wn = FEW ? 0 : wave % WN;
   const int H = a.H, W = a.W, C = a.C, S = a.S;
   const int Ho = GM ? a.Ho : H, Wo = GM ? a.Wo : W;
   const int sd = GM ? a.stride : 1;
@@ -235,9 +249,23 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int 
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
 
+  f32x4_t acc4 = {0.f, 0.f, 0.f, 0.f};  // FEW
+
   // fragment of a 32-row, 16-deep slice: lane l holds row l % 32, elements 8 (l / 32) .. + 8
   const int frow = lane & 31, fsw = BK == 64 ? frow & 7 : (frow >> 1) & 3;
   auto multiply = [&](auto I) __attribute__((always_inline)) {
+    if constexpr (FEW) {
+      // 16 rows, 32 deep: lane l holds row l % 16, elements 8 (l / 16) .. + 8
+      const bf16_t* sa = stage(I) + ((wave >> 1) * 16 + (lane & 15)) * BK;
+      const bf16_t* sb = stage(I) + (BM + (wave & 1) * 16 + (lane & 15)) * BK;
+#pragma unroll
+      for (int kk = 0; kk < BK / 32; ++kk) {
+        const int p = ((kk * 4 + (lane >> 4)) ^ (lane & 7)) * 8;
+        const bf16x8_t af = *reinterpret_cast<const bf16x8_t*>(sa + p), bf = *reinterpret_cast<const bf16x8_t*>(sb + p);
+        acc4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, acc4, 0, 0, 0);
+      }
+      return;
+    }
     const bf16_t* sa = stage(I) + (wm * WTM + frow) * BK;
     const bf16_t* sb = stage(I) + (BM + wn * WTN + frow) * BK;
 #pragma unroll
@@ -257,28 +285,45 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int 
   };
 
   if (nk > 0) {
-    static_for<0, NS - 1>([&](auto I) __attribute__((always_inline)) { copy(I); });
+    // steps are copied and multiplied U at a time, one barrier each
+    constexpr int U = FEW ? UF : 1;
+    static_assert(NS % U == 0 && NS >= 2 * U, "whole groups of buffers");
+    static_for<0, NS - U>([&](auto I) __attribute__((always_inline)) { copy(I); });
     int k = 0;
     while (true) {
       bool done = false;
-      static_for<0, NS>([&](auto I) __attribute__((always_inline)) {
-        constexpr int i = decltype(I)::value;
+      static_for<0, NS / U>([&](auto G) __attribute__((always_inline)) {
+        constexpr int g = decltype(G)::value * U;
         if (!done) {
-          // this wave's copies of step k have landed; past the barrier so have
-          // the others', and all waves have read the buffer that is refilled
-          wait_vm<(NS - 2) * LOADS>();
-          wg_barrier();
-          copy(std::integral_constant<int, (i + NS - 1) % NS>{});
+          // this wave's copies of these steps have landed; past the barrier so
+          // have the others', and all waves have read the buffers that are refilled
+          wait_step<(NS - 2 * U) * LOADS>();
+          static_for<0, U>([&](auto J) __attribute__((always_inline)) {
+            copy(std::integral_constant<int, (g + NS - U + decltype(J)::value) % NS>{});
+          });
           __builtin_amdgcn_sched_barrier(0);  // (left to itself the compiler issues the copies last)
-          multiply(I);
-          done = ++k == nk;
+          static_for<0, U>([&](auto J) __attribute__((always_inline)) {
+            constexpr int j = decltype(J)::value;
+            if (j == 0 || k + j < nk) multiply(std::integral_constant<int, g + j>{});
+          });
+          k += U;
+          done = k >= nk;
         }
       });
       if (done) break;
     }
-    wait_vm<0>();
   }
-  wg_barrier();
+  wait_step<0>();
+  if constexpr (FEW) {
+    // the four results to the finishing wave, as its 32x32 result
+    float* red = reinterpret_cast<float*>(st1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      red[((wave >> 1) * 16 + 4 * (lane >> 4) + q) * 32 + (wave & 1) * 16 + (lane & 15)] = acc4[q];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][0][r] = red[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 32 + (lane & 31)];
+  }
 
   // ------------------------------------------------------------- epilogue
   // Each wave finishes its tile in strips of rows through its own part of LDS
@@ -287,7 +332,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int 
   // registers over the wave's rows and then across lanes and waves in a fixed
   // order.
   constexpr int CW = WTN / 8;                         // 8-column chunks per strip row
-  constexpr int SR = SZ0 >= NW * WTN * 64 ? 32 : 16;  // strip rows
+  constexpr int SR = SZ0 >= WM * WN * WTN * 64 ? 32 : 16;  // strip rows
   constexpr int PASS = SR * CW / 64;                  // chunks per lane and strip
   constexpr int LPR = 64 / CW;                        // rows per pass
   constexpr int STRIPS = TM * 32 / SR;
@@ -308,7 +353,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int 
     // Forward: a lane holds a column of each 32x32 result (16 rows of it), so
     // bias, ReLU, the rounding and the column sums are taken there, and the
     // strip goes through LDS as bf16.
-    bf16_t* ot = st0 + wave * (SR * WTN);
+    bf16_t* ot = st0 + (FEW ? 0 : wave) * (SR * WTN);
     float bias[TN];
     double s0[TN], s1[TN];
 #pragma unroll
@@ -320,7 +365,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int 
     const int rows = M - m0 - wm * WTM;  // rows of this wave's tile that exist
     const bool cut = a.bias && rows < WTM;
 #pragma unroll
-    for (int t = 0; t < STRIPS; ++t) {
+    for (int t = 0; t < (finish ? STRIPS : 0); ++t) {
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -365,7 +410,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int 
     for (int j = 0; j < TN; ++j) {
       s0[j] += __shfl_xor(s0[j], 32, 64);
       s1[j] += __shfl_xor(s1[j], 32, 64);
-      if (lane < 32) {
+      if (finish && lane < 32) {
         sred[wm][0][wn * WTN + j * 32 + lane] = s0[j];
         sred[wm][1][wn * WTN + j * 32 + lane] = s1[j];
       }
@@ -374,7 +419,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int 
     // Data gradient: mask, earlier contribution and batch-norm input come in
     // 16-byte chunks, so the fp32 strip goes through LDS and a lane finishes
     // chunks of one chunk column.
-    float* ot = reinterpret_cast<float*>(st0) + wave * (SR * WTN);
+    float* ot = reinterpret_cast<float*>(st0) + (FEW ? 0 : wave) * (SR * WTN);
     const bf16_t* mask = (const bf16_t*)a.mask;
     const bf16_t* z = nullptr;  // input of the batch norm whose output gradient these columns are
     const double *mean = nullptr, *rstd = nullptr;
@@ -393,7 +438,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int 
 #pragma unroll
     for (int e = 0; e < 16; ++e) v[e] = 0.0;
 #pragma unroll
-    for (int t = 0; t < STRIPS; ++t) {
+    for (int t = 0; t < (finish ? STRIPS : 0); ++t) {
       u32x4_t c_mask[PASS], c_old[PASS], c_z[PASS];
       int c_m[PASS];
 #pragma unroll
@@ -473,7 +518,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int 
     }
 #pragma unroll
     for (int e = 0; e < 2; ++e)
-      if (e < nv) sred[wm][(idx + e) >> 3][wn * WTN + ch * 8 + ((idx + e) & 7)] = v[e];
+      if (e < nv && finish) sred[wm][(idx + e) >> 3][wn * WTN + ch * 8 + ((idx + e) & 7)] = v[e];
   }
   __syncthreads();
   double* part = DG ? a.bn_part : a.stat_part;
@@ -487,7 +532,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int 
   }
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int NS, bool RAG, int GM, bool DG = GM == 2>
+template <int BM, int BN, int WM, int WN, int BK, int NS, bool RAG, int GM, bool DG = GM == 2, bool FEW = false, int UF = 1>
 hipError_t go(const ConvArgs& a, hipStream_t s, int* row_tiles) {
   int tiles = 0;
   if (GM == 2) {
@@ -501,14 +546,14 @@ hipError_t go(const ConvArgs& a, hipStream_t s, int* row_tiles) {
   const double rows = GM == 1 ? (double)a.Ho * a.Wo : (double)a.H * a.W;  // (GM 2: each dy pixel meets each tap)
   const double flops = 2.0 * a.nb * rows * a.N * a.R * a.S * a.C;
   static const struct Name {
-    char s[72];
+    char s[80];
     Name() {
-      snprintf(s, sizeof s, "k_conv_gemm_lds<%d,%d,%d,%d,%d,%d,%s,%d,%s>", BM, BN, WM, WN, BK, NS,
-               RAG ? "true" : "false", GM, DG ? "true" : "false");
+      snprintf(s, sizeof s, "k_conv_gemm_lds<%d,%d,%d,%d,%d,%d,%s,%d,%s,%s>", BM, BN, WM, WN, BK, NS,
+               RAG ? "true" : "false", GM, DG ? "true" : "false", FEW ? "true" : "false");
     }
   } name;
-  XP_LAUNCH(name.s, flops, (k_conv_gemm_lds<BM, BN, WM, WN, BK, NS, RAG, GM, DG>), dim3(tiles * ((a.N + BN - 1) / BN)),
-            dim3(WM * WN * 64), 0, s, a, tiles);
+  XP_LAUNCH(name.s, flops, (k_conv_gemm_lds<BM, BN, WM, WN, BK, NS, RAG, GM, DG, FEW, UF>),
+            dim3(tiles * ((a.N + BN - 1) / BN)), dim3(FEW ? 256 : WM * WN * 64), 0, s, a, tiles);
   return hipGetLastError();
 }
 
@@ -554,6 +599,21 @@ hipError_t pick_step(const ConvArgs& a, int64_t rows, hipStream_t s, int* row_ti
                        : pick_tile<true, GM, DG>(a, rows, s, row_tiles);
 }
 
+// Few tiles: 32x32, four buffers, or eight where the reduction is so long that
+// its operands' path is the limit (us per launch, general kernel's 32x64 tiles
+// before: 3x3 512->512 at 4x4x32 16.1 with eight and 20.5 with four, 20.6; 3x3 128->128
+// at 8x8x32 6.8, 8.0; 7x1 160->192 at 12x12x4 7.3, 13.1; 1x1 352->128 at 14x14x12
+// 5.6, 7.2; linear 2048->200 over 100 rows 8.7, 10.8; 3x3 stride 2 256->256 at
+// 28x28x8 12.0, 22.0).  One chain of sums per element keeps the stored bits of
+// the other tiles; the reduction split over eight waves took 12.1 us on the
+// first of these, but other bits flip ReLU and pool decisions downstream.
+template <int GM, bool DG>
+hipError_t few(const ConvArgs& a, hipStream_t s, int* row_tiles) {
+  if (a.C % 64 != 0) return go<32, 32, 1, 1, 64, 4, true, GM, DG, true, 2>(a, s, row_tiles);
+  if ((int64_t)a.R * a.S * a.C >= 4096) return go<32, 32, 1, 1, 64, 8, false, GM, DG, true, 2>(a, s, row_tiles);
+  return go<32, 32, 1, 1, 64, 4, false, GM, DG, true, 2>(a, s, row_tiles);
+}
+
 }  // namespace
 
 bool launch_conv_lds(const ConvArgs& a, hipStream_t s, int* row_tiles, hipError_t* e) {
@@ -572,18 +632,20 @@ bool launch_conv_lds(const ConvArgs& a, hipStream_t s, int* row_tiles, hipError_
   if (a.bn_part)
     for (int k = 0; k < a.bn_nseg; ++k)
       fits = fits && a.bn_c0[k] % 8 == 0 && a.bn_c1[k] % 8 == 0 && (!a.bn_z[k] || chunks16(a.bn_z[k], a.ld_bnz[k]));
-  // fewer tiles than CUs: the general kernel's smaller tiles give more
-  // (3x3 512->512 at 4x4x32, 64 tiles: 34.8 against 20.7 us; 3x3 256->256 at
-  // 8x8x32, 128 tiles: 13.8 against 12.8; 3x3 128->128 at 16x16x32, 256 tiles:
-  // 9.7 against 11.5)
-  fits = fits && tiles(rows, 64, a.N, a.N <= 32 ? 32 : 64) >= 192;
   // the residue classes' last tiles stay within conv_max_row_tiles
   fits = fits && (!a.tr || rows >= 256);
-  if (!fits) return false;
+  if (!fits || (grid && dg && !a.tr)) return false;
   ConvArgs b = a;
   b.stride = stride;
+  // fewer 64x64 tiles than CUs (a data gradient by residue classes keeps
+  // them: 3x3 stride 2, 256->256 at 14x14x8, 14.1 against 15.7 us)
+  if (!a.tr && tiles(rows, 64, a.N, a.N <= 32 ? 32 : 64) < 192) {
+    if (grid) *e = few<1, false>(b, s, row_tiles);
+    else if (dg) *e = few<0, true>(b, s, row_tiles);
+    else *e = few<0, false>(b, s, row_tiles);
+    return true;
+  }
   if (a.tr) *e = pick_step<2, true>(b, rows, s, row_tiles);
-  else if (grid && dg) return false;
   else if (grid) *e = pick_step<1, false>(b, rows, s, row_tiles);
   else if (dg) *e = pick_step<0, true>(b, rows, s, row_tiles);
   else *e = pick_step<0, false>(b, rows, s, row_tiles);

@@ -39,6 +39,13 @@ CASES = {
     "strided_1x1": ([conv(-1, 256, 512, 1, stride=2)], (81, 80, 256), 4),
     "strided_7x7_chunk_taps": ([conv(-1, 40, 256, 7, stride=2)], (57, 56, 40), 4),
     "unpadded": ([conv(-1, 64, 256, 5, pad="valid")], (33, 32, 64), 4),
+    # few tiles: 32 x 32, four or eight buffers
+    "few_tiles": ([conv(-1, 64, 64, 3, True), relu(0)], (7, 7, 64), 3),
+    "few_tiles_long": ([conv(-1, 512, 48, 3, True), relu(0)], (7, 7, 512), 3),
+    "few_tiles_chunk_taps": ([conv(-1, 24, 40, 7), bn(0, 40)], (9, 11, 24), 3),
+    "few_tiles_one_step": ([conv(-1, 40, 8, 1)], (9, 11, 40), 3),
+    "few_tiles_bn_partials": ([conv(-1, 64, 128, 1), bn(0, 128), relu(1), conv(2, 128, 64, 5)], (9, 10, 64), 3),
+    "few_tiles_strided": ([conv(-1, 64, 64, 3, stride=2)], (23, 25, 64), 2),
     # data gradients with mask, accumulation and batch-norm backward partials
     "bn_partials": ([conv(-1, 64, 256, 1), bn(0, 256), relu(1), conv(2, 256, 64, 3), bn(3, 64), conv(2, 256, 72, 1),
                      dict(kind="concat", inputs=[4, 5])], (57, 57, 64), 4),
