@@ -339,6 +339,18 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
   const int ch = lane % CW, n = n0 + wn * WTN + ch * 8;
   const bool live_n = n < a.N;
   bf16_t* y = (bf16_t*)a.y;
+  const bf16_t* mask = (const bf16_t*)a.mask;
+  // mean and 1 / deviation of the batch norm that column tid belongs to
+  double col_mean = 0.0, col_rstd = 0.0;
+  if (DG && a.bn_part && tid < BN && n0 + tid < a.N) {
+    const int c = n0 + tid;
+#pragma unroll
+    for (int q = 0; q < CONV_BN_SEGS; ++q)
+      if (q < a.bn_nseg && c >= a.bn_c0[q] && c < a.bn_c1[q] && a.bn_z[q]) {
+        col_mean = a.bn_mean[q][c - a.bn_c0[q]];
+        col_rstd = a.bn_rstd[q][c - a.bn_c0[q]];
+      }
+  }
   // output pixel of the lane's chunk of pass p in strip t, or -1
   auto out_row = [&](int t, int p) __attribute__((always_inline)) -> int {
     const int m = m0 + wm * WTM + t * SR + p * LPR + lane / CW;
@@ -348,6 +360,47 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
       return (img * Ho + oy + h * od) * Wo + ox + w * od;
     }
     return m;
+  };
+  const int n_in = live_n ? n : 0;
+  // input of the batch norm whose output gradient these columns are (else any
+  // readable chunk, whose sums are not kept)
+  const bf16_t* z = (const bf16_t*)a.x;
+  int ldz = 0;
+  bool has_z = false;
+  if (DG && a.bn_part && live_n) {
+#pragma unroll
+    for (int q = 0; q < CONV_BN_SEGS; ++q)
+      if (q < a.bn_nseg && n >= a.bn_c0[q] && n < a.bn_c1[q] && a.bn_z[q]) {
+        z = (const bf16_t*)a.bn_z[q] + (n - a.bn_c0[q]);
+        ldz = a.ld_bnz[q];
+        has_z = true;
+      }
+  }
+  // a data gradient's operands in 16-byte chunks: mask, earlier contribution,
+  // batch-norm input
+  u32x4_t c_mask[PASS], c_old[PASS], c_z[PASS];
+  int c_m[PASS];
+  // loads of strip t (rows and columns past the end read the first ones: guarded
+  // per lane the compiler waits for each before the next)
+  auto fetch = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int p = 0; p < PASS; ++p) {
+      c_m[p] = out_row(t, p);
+      c_mask[p] = (u32x4_t){0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};  // no mask: all positive
+      c_old[p] = c_z[p] = (u32x4_t){0u, 0u, 0u, 0u};
+    }
+    if (mask)
+#pragma unroll
+      for (int p = 0; p < PASS; ++p)
+        c_mask[p] = *reinterpret_cast<const u32x4_t*>(mask + (size_t)max(c_m[p], 0) * a.ldm + n_in);
+    if (a.accumulate)
+#pragma unroll
+      for (int p = 0; p < PASS; ++p)
+        c_old[p] = *reinterpret_cast<const u32x4_t*>(y + (size_t)max(c_m[p], 0) * a.ldy + n_in);
+    if (a.bn_part)
+#pragma unroll
+      for (int p = 0; p < PASS; ++p)
+        c_z[p] = *reinterpret_cast<const u32x4_t*>(z + (size_t)max(c_m[p], 0) * ldz);
   };
   if constexpr (!DG) {
     // Forward: a lane holds a column of each 32x32 result (16 rows of it), so
@@ -420,37 +473,12 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
     // 16-byte chunks, so the fp32 strip goes through LDS and a lane finishes
     // chunks of one chunk column.
     float* ot = reinterpret_cast<float*>(st0) + (FEW ? 0 : wave) * (SR * WTN);
-    const bf16_t* mask = (const bf16_t*)a.mask;
-    const bf16_t* z = nullptr;  // input of the batch norm whose output gradient these columns are
-    const double *mean = nullptr, *rstd = nullptr;
-    int ldz = 0;
-    if (a.bn_part && live_n) {
-#pragma unroll
-      for (int q = 0; q < CONV_BN_SEGS; ++q)
-        if (q < a.bn_nseg && n >= a.bn_c0[q] && n < a.bn_c1[q] && a.bn_z[q]) {
-          z = (const bf16_t*)a.bn_z[q] + (n - a.bn_c0[q]);
-          mean = a.bn_mean[q] + (n - a.bn_c0[q]);
-          rstd = a.bn_rstd[q] + (n - a.bn_c0[q]);
-          ldz = a.ld_bnz[q];
-        }
-    }
     double v[16];  // column sums: of g, then of g z
 #pragma unroll
     for (int e = 0; e < 16; ++e) v[e] = 0.0;
 #pragma unroll
     for (int t = 0; t < (finish ? STRIPS : 0); ++t) {
-      u32x4_t c_mask[PASS], c_old[PASS], c_z[PASS];
-      int c_m[PASS];
-#pragma unroll
-      for (int p = 0; p < PASS; ++p) {
-        const int m = c_m[p] = out_row(t, p);
-        c_mask[p] = c_old[p] = c_z[p] = (u32x4_t){0u, 0u, 0u, 0u};
-        if (m >= 0) {
-          if (mask) c_mask[p] = *reinterpret_cast<const u32x4_t*>(mask + (size_t)m * a.ldm + n);
-          if (a.accumulate) c_old[p] = *reinterpret_cast<const u32x4_t*>(y + (size_t)m * a.ldy + n);
-          if (z) c_z[p] = *reinterpret_cast<const u32x4_t*>(z + (size_t)m * ldz);
-        }
-      }
+      fetch(t);
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -470,13 +498,18 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
         float f[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
+          const uint32_t mw = c_mask[p][e >> 1];
+          const float x = e < 4 ? lo[e] : hi[e - 4];
+          f[e] = __uint_as_float((e & 1) ? (mw & 0xffff0000u) : (mw << 16)) > 0.0f ? x : 0.f;
+        }
+        if (a.accumulate) {
           // one fp32 rounding of acc + y equals the rounding of their exact
           // double sum (53 >= 2 * 24 + 2)
-          float x = e < 4 ? lo[e] : hi[e - 4];
-          const uint32_t mw = c_mask[p][e >> 1], ow = c_old[p][e >> 1];
-          if (mask && !(__uint_as_float((e & 1) ? (mw & 0xffff0000u) : (mw << 16)) > 0.0f)) x = 0.f;
-          if (a.accumulate) x += __uint_as_float((e & 1) ? (ow & 0xffff0000u) : (ow << 16));
-          f[e] = x;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const uint32_t ow = c_old[p][e >> 1];
+            f[e] += __uint_as_float((e & 1) ? (ow & 0xffff0000u) : (ow << 16));
+          }
         }
         u32x4_t pr;
 #pragma unroll
@@ -488,7 +521,7 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
             // the stored gradient, as what reads it sees it
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-              const uint32_t w = pr[e >> 1], zw = c_z[p][e >> 1];
+              const uint32_t w = pr[e >> 1], zw = has_z ? c_z[p][e >> 1] : 0u;
               const double g = (double)__uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
               v[e] += g;
               v[8 + e] += g * (double)__uint_as_float((e & 1) ? (zw & 0xffff0000u) : (zw << 16));
@@ -498,22 +531,19 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
       }
     }
     if (!a.bn_part) return;
-    // sum of g (z - mean) rstd; the products are exact in fp64, and a bf16 z
-    // bounds what the difference can cancel (mean / deviation below 2^9)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[8 + e] = z ? (v[8 + e] - mean[e] * v[e]) * rstd[e] : 0.0;
     // add across the lanes of one chunk column, halving the values a lane keeps
     int idx = 0, nv = 16;
 #pragma unroll
     for (int st = 32; st >= CW; st >>= 1) {
       const bool hi = (lane & st) != 0;
       nv >>= 1;
+      double got[8];  // (all of a level's exchanges before its sums: one wait)
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (e < nv) {
-          const double send = hi ? v[e] : v[e + nv], keep = hi ? v[e + nv] : v[e];
-          v[e] = keep + __shfl_xor(send, st, 64);
-        }
+        if (e < nv) got[e] = __shfl_xor(hi ? v[e] : v[e + nv], st, 64);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (e < nv) v[e] = (hi ? v[e + nv] : v[e]) + got[e];
       idx += hi ? nv : 0;
     }
 #pragma unroll
@@ -522,13 +552,20 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
   }
   __syncthreads();
   double* part = DG ? a.bn_part : a.stat_part;
-  for (int q = tid; q < 2 * BN; q += NW * 64) {
-    const int which = q / BN, col = q - which * BN;
-    if (n0 + col >= a.N) continue;
-    double s = 0.0;
+  static_assert(BN <= NW * 64, "a column per thread");
+  if (tid < BN && n0 + tid < a.N) {
+    double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-    for (int w = 0; w < WM; ++w) s += sred[w][which][col];
-    part[((size_t)(n0 + col) * 2 + which) * tiles_m + tm] = s;
+    for (int w = 0; w < WM; ++w) {
+      s0 += sred[w][0][tid];
+      s1 += sred[w][1][tid];
+    }
+    // sum of g (z - mean) rstd from the sums of g z and g: the products are
+    // exact in fp64, and a bf16 z bounds what the difference can cancel
+    // (mean / deviation below 2^9); a bias's columns have no z, second sum 0
+    if (DG) s1 = (s1 - col_mean * s0) * col_rstd;
+    part[((size_t)(n0 + tid) * 2 + 0) * tiles_m + tm] = s0;
+    part[((size_t)(n0 + tid) * 2 + 1) * tiles_m + tm] = s1;
   }
 }
 
@@ -568,23 +605,27 @@ int64_t tiles(int64_t rows, int bm, int cols, int bn) { return ((rows + bm - 1) 
 //  - wider: 128x128 on eight waves while it gives 400 tiles (1x1 256->1024 at
 //    14x14x100: 27.4, 64x128 30.6; below that, 3x3 256->256 there, 306 tiles:
 //    41.3 against 38.1), then 64x128, then 64x64 (3x3 512->512 at 7x7x100:
-//    43.8 / 39.5); 64 columns where 128 would pad by more than a quarter
-//    (1x1 256->176: 15.4 against 16.8);
-//  - a data gradient over very many rows and 256 columns or a multiple, whose
-//    time is its epilogue's four tensors, takes rows of 256 columns in one
+//    43.8 / 39.5); 64 columns where 128 would pad by more than an eighth
+//    (1x1 256->176: 15.4 against 16.8; 7x1 32->320 at 11x11x102: 10.5 / 11.5);
+//  - a data gradient's epilogue (up to four tensors, fp64 sums) costs most per
+//    workgroup, so it keeps the larger tiles for longer (1x1 256->1024 at
+//    14x14x32, accumulated: 128x128 15.2, 64x64 31; 3x3 256->256 at 14x14x100:
+//    41.4, 64x128 45.6), and over very many rows takes 256 columns in one
 //    workgroup (1x1 64->256 at 56x56x100: 131, 128x128 150).
 // Two buffers: a third or fourth lost more workgroups per CU than it hid.
 template <bool RAG, int GM, bool DG>
 hipError_t pick_tile(const ConvArgs& a, int64_t rows, hipStream_t s, int* row_tiles) {
   if (a.N <= 32) return go<128, 32, 4, 1, 64, 2, RAG, GM, DG>(a, s, row_tiles);
   const int64_t pad64 = (a.N + 63) / 64 * 64, pad128 = (a.N + 127) / 128 * 128;
-  if (a.N > 96 && 4 * pad128 <= 5 * pad64) {
+  if (a.N > 96 && 8 * pad128 <= 9 * pad64) {
     if constexpr (DG && GM == 0)
       if (a.N % 256 == 0 && tiles(rows, 256, a.N, 256) >= 1024)
         return go<256, 256, 2, 4, 64, 2, RAG, GM, DG>(a, s, row_tiles);
-    if (tiles(rows, 128, a.N, 128) >= 400) return go<128, 128, 4, 2, 64, 2, RAG, GM, DG>(a, s, row_tiles);
-    if (tiles(rows, 64, a.N, 128) >= 400) return go<64, 128, 2, 2, 64, 2, RAG, GM, DG>(a, s, row_tiles);
-  } else if (tiles(rows, 128, a.N, 64) >= 512) {
+    if (tiles(rows, 128, a.N, 128) >= (DG ? 192 : 400))
+      return go<128, 128, 4, 2, 64, 2, RAG, GM, DG>(a, s, row_tiles);
+    if (tiles(rows, 64, a.N, 128) >= (DG ? 192 : 400))
+      return go<64, 128, 2, 2, 64, 2, RAG, GM, DG>(a, s, row_tiles);
+  } else if (tiles(rows, 128, a.N, 64) >= (DG ? 256 : 512)) {
     if (a.N > 64 && a.N <= 96) return go<96, 96, 1, 3, 32, 3, RAG, GM, DG>(a, s, row_tiles);
     return go<128, 64, 4, 2, 64, 2, RAG, GM, DG>(a, s, row_tiles);
   }
@@ -594,7 +635,7 @@ hipError_t pick_tile(const ConvArgs& a, int64_t rows, hipStream_t s, int* row_ti
 template <int GM, bool DG>
 hipError_t pick_step(const ConvArgs& a, int64_t rows, hipStream_t s, int* row_tiles) {
   // (the 96x96 tile steps by 32 channels)
-  const int bk = a.N > 64 && a.N <= 96 && tiles(rows, 128, a.N, 64) >= 512 ? 32 : 64;
+  const int bk = a.N > 64 && a.N <= 96 && tiles(rows, 128, a.N, 64) >= (DG ? 256 : 512) ? 32 : 64;
   return a.C % bk == 0 ? pick_tile<false, GM, DG>(a, rows, s, row_tiles)
                        : pick_tile<true, GM, DG>(a, rows, s, row_tiles);
 }
@@ -637,11 +678,32 @@ bool launch_conv_lds(const ConvArgs& a, hipStream_t s, int* row_tiles, hipError_
   if (!fits || (grid && dg && !a.tr)) return false;
   ConvArgs b = a;
   b.stride = stride;
-  // fewer 64x64 tiles than CUs (a data gradient by residue classes keeps
-  // them: 3x3 stride 2, 256->256 at 14x14x8, 14.1 against 15.7 us)
-  if (!a.tr && tiles(rows, 64, a.N, a.N <= 32 ? 32 : 64) < 192) {
+  const int64_t K = (int64_t)a.R * a.S * a.C;
+  const int cols = a.N <= 32 ? 32 : 64;
+  if (dg && !a.tr) {
+    // small data gradients, where the epilogue counts for more than the loop,
+    // stay with the general kernel (1x1 256->512 at 14x14x8: 6.8, here 8.8 us; 1x1
+    // 256->512 at 14x14x16: 9.2 / 9.8; 3x3 128->128 at 16x16x32: 12.0 / 12.8; 3x3 64->64
+    // at 28x28x16: 8.4 / 10.1) unless the reduction is long (1x1 1024->256 at
+    // 14x14x32: 20.0 / 15.0; 3x3 256->256 at 14x14x16: 18.6 / 17.5; 3x3
+    // 512->512 at 4x4x32: 21.5 / 19.4)
+    const bool wide = a.N > 96;
+    const bool many = wide ? tiles(rows, 128, a.N, 128) >= 192 : tiles(rows, 128, a.N, cols) >= 256;
+    if (!many) {
+      if (wide && K >= 1024 && tiles(rows, 64, a.N, 128) >= 192) {
+      } else if (K >= 2048 && tiles(rows, 64, a.N, cols) >= 192) {
+      } else if (K >= 4096 && tiles(rows, 64, a.N, cols) < 192) {
+        *e = few<0, true>(b, s, row_tiles);
+        return true;
+      } else {
+        return false;
+      }
+    }
+  } else if (!a.tr && tiles(rows, 64, a.N, cols) < 192 && (K > 256 || tiles(rows, 64, a.N, cols) < 96)) {
+    // fewer 64x64 tiles than CUs (two or four steps: not far fewer, 1x1 128->512
+    // over 1000 rows, 128 tiles: 4.5 against 4.8 us; a data gradient by residue
+    // classes keeps them: 3x3 stride 2, 256->256 at 14x14x8, 14.1 / 15.7)
     if (grid) *e = few<1, false>(b, s, row_tiles);
-    else if (dg) *e = few<0, true>(b, s, row_tiles);
     else *e = few<0, false>(b, s, row_tiles);
     return true;
   }
