@@ -1006,289 +1006,6 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
 }
 
 
-// bf16 weight gradient, 16-byte chunk path (channels, output channels and row
-// strides multiples of 8, views below 2 GiB), 32x32 wave tiles.  The operands
-// load through raw buffer resources (out-of-range offsets read zeros),
-// addresses advance by a scalar per step, each thread tracks the image row /
-// column of its pixel incrementally, and PF steps of loads are in flight.
-// The reduction runs over pixels, which are the rows of both operands in
-// memory, while an MFMA fragment holds 8 consecutive pixels of one column: the
-// tiles therefore sit in LDS as loaded (one row per pixel, 16-byte stores) and
-// the fragments are read with gfx950's transposing LDS read.  Interleaving
-// pixel pairs into column-major rows on the way into LDS instead (two
-// permutes and two 4-byte LDS stores per 16 loaded bytes) was 30% slower on
-// the 3x3 and 5x5 stage shapes (3x3 64 -> 96: 35.4 -> 24.6 us with the split
-// reduction), with the same bits.
-// GRID: dz lives on the Ho x Wo grid of a strided or unpadded convolution (or
-// the rows and columns pad differently); each pixel then tracks its image, row
-// and column and addresses x at (ho*stride + r - pad, wo*stride + q - padw)
-template <int BM, int BN, int WM, int WN, int PF, bool GRID>
-__global__ __launch_bounds__(256) void k_wgrad_t(WgradArgs a) {
-  using T = bf16_t;
-  // 64 pixels per step: four 32x32x16 MFMAs per wave between barriers (32 took
-  // 4-8% longer on the stage shapes)
-  constexpr int VEC = 8, BKm = 64, RPT = 1;
-  // rows = pixels, as loaded; a row pitch of 32 bytes over the tile width puts
-  // the four rows one transposing read touches in disjoint banks
-  constexpr int PA = BM + 16, PB = BN + 16;
-  __shared__ __align__(16) T sA[2][BKm * PA];
-  __shared__ __align__(16) T sB[2][BKm * PB];
-  constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 16, TN = WTN / 16;
-  static_assert(WM * WN == 4, "four waves");
-  constexpr int A_T = BKm * (BM / VEC), B_T = BKm * (BN / VEC);
-  constexpr int A_PER = (A_T + 255) / 256, B_PER = (B_T + 255) / 256;
-  constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const int H = a.H, W = a.W, C = a.C, S = a.S, pad = a.pad, N = a.N;
-  const int padw = GRID ? a.padw : pad;
-  const int sd = GRID && a.stride > 1 ? a.stride : 1;
-  const int Ho = GRID && a.Ho > 0 ? a.Ho : H, Wo = GRID && a.Ho > 0 ? a.Wo : W;
-  const int M = a.nb * Ho * Wo;    // dz pixels
-  const int Min = a.nb * H * W;    // x pixels
-  const int K = a.R * S * C;
-  const int n0 = blockIdx.x * BM, k0 = blockIdx.y * BN;
-  const int mps = ((M + a.splits - 1) / a.splits + BKm - 1) / BKm * BKm;
-  const int mbeg = blockIdx.z * mps;
-  const int mend = min(M, mbeg + mps);
-  const __amdgpu_buffer_rsrc_t dr = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)a.dz, (short)0, (int)((((size_t)(M - 1)) * a.lddz + N) * sizeof(T)), 0x00020000);
-  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)a.x, (short)0, (int)((((size_t)(Min - 1)) * a.ldx + C) * sizeof(T)), 0x00020000);
-
-  // A tasks (dz): pixel pair p, output-channel chunk c
-  int a_p[A_PER], a_c[A_PER];
-  uint32_t a_off[A_PER];
-  bool a_slot[A_PER], a_nok[A_PER];
-#pragma unroll
-  for (int i = 0; i < A_PER; ++i) {
-    const int q = tid + i * 256;
-    a_slot[i] = q < A_T;
-    a_c[i] = q % (BM / VEC);
-    a_p[i] = q / (BM / VEC);
-    const int n = n0 + a_c[i] * VEC;
-    a_nok[i] = a_slot[i] && n < N;
-    a_off[i] = (uint32_t)((((size_t)mbeg + a_p[i] * RPT) * a.lddz + n) * sizeof(T));
-  }
-  // B tasks (x): pixel pair p, reduction chunk (tap r, s, channel ch)
-  int b_p[B_PER], b_c[B_PER], b_r[B_PER], b_s[B_PER], b_ch[B_PER];
-  int b_h[B_PER][RPT], b_w[B_PER][RPT], b_img[B_PER][RPT];
-  uint32_t b_off[B_PER];
-  bool b_slot[B_PER], b_kok[B_PER];
-#pragma unroll
-  for (int i = 0; i < B_PER; ++i) {
-    const int q = tid + i * 256;
-    b_slot[i] = q < B_T;
-    b_c[i] = q % (BN / VEC);
-    b_p[i] = q / (BN / VEC);
-    const int kk = k0 + b_c[i] * VEC;
-    b_kok[i] = b_slot[i] && kk < K;
-    const int rs = b_kok[i] ? kk / C : 0, ch = b_kok[i] ? kk - rs * C : 0;
-    b_r[i] = rs / S;
-    b_s[i] = rs - b_r[i] * S;
-    b_ch[i] = ch;
-    // byte offset of (first pixel of the pair at step 0, shifted by the tap)
-    const long long pix = (long long)mbeg + b_p[i] * RPT + (b_r[i] - pad) * W + (b_s[i] - pad);
-    b_off[i] = GRID ? 0u : (uint32_t)((pix * a.ldx + ch) * (long long)sizeof(T));
-#pragma unroll
-    for (int u = 0; u < RPT; ++u) {
-      const int m = mbeg + b_p[i] * RPT + u;
-      const int rem = m % (Ho * Wo);
-      b_img[i][u] = m / (Ho * Wo);
-      b_h[i][u] = rem / Wo;
-      b_w[i][u] = rem - b_h[i][u] * Wo;
-    }
-  }
-
-  uint4 ra[PF][A_PER][RPT], rb[PF][B_PER][RPT];
-  int loaded = 0;  // steps loaded so far
-
-  auto gload = [&](auto SLOT) __attribute__((always_inline)) {
-    constexpr int slot = decltype(SLOT)::value;
-    const int mb = loaded * BKm;  // pixel offset of this step from mbeg
-    const int left = mend - mbeg - mb;
-#pragma unroll
-    for (int i = 0; i < A_PER; ++i)
-#pragma unroll
-      for (int u = 0; u < RPT; ++u) {
-        const bool ok = a_nok[i] && a_p[i] * RPT + u < left;
-        const uint32_t off =
-            ok ? a_off[i] + (uint32_t)(((size_t)mb + u) * a.lddz * sizeof(T)) : OUT_OF_RANGE;
-        const auto v = __builtin_amdgcn_raw_buffer_load_b128(dr, (int)off, 0, 0);
-        ra[slot][i][u] = make_uint4(v[0], v[1], v[2], v[3]);
-      }
-#pragma unroll
-    for (int i = 0; i < B_PER; ++i)
-#pragma unroll
-      for (int u = 0; u < RPT; ++u) {
-        const int hh = b_h[i][u] * sd + b_r[i] - pad, ww = b_w[i][u] * sd + b_s[i] - padw;
-        const bool ok = b_kok[i] && b_p[i] * RPT + u < left && (unsigned)hh < (unsigned)H &&
-                        (unsigned)ww < (unsigned)W;
-        uint32_t off;
-        if constexpr (GRID)
-          off = ok ? (uint32_t)(((((size_t)b_img[i][u] * H + hh) * W + ww) * a.ldx + b_ch[i]) * sizeof(T))
-                   : OUT_OF_RANGE;
-        else
-          off = ok ? b_off[i] + (uint32_t)(((size_t)mb + u) * a.ldx * sizeof(T)) : OUT_OF_RANGE;
-        const auto v = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)off, 0, 0);
-        rb[slot][i][u] = make_uint4(v[0], v[1], v[2], v[3]);
-        // advance this pixel by one step
-        int w2 = b_w[i][u] + BKm, h2 = b_h[i][u];
-        while (w2 >= Wo) {
-          w2 -= Wo;
-          if (++h2 == Ho) {
-            h2 = 0;
-            if constexpr (GRID) ++b_img[i][u];
-          }
-        }
-        b_w[i][u] = w2;
-        b_h[i][u] = h2;
-      }
-    ++loaded;
-  };
-
-  // each task's 16 bytes (8 channels of one pixel) go to its pixel's row as
-  // loaded: no interleaving
-  auto lstore = [&](auto SLOT, int buf) __attribute__((always_inline)) {
-    constexpr int slot = decltype(SLOT)::value;
-#pragma unroll
-    for (int i = 0; i < A_PER; ++i)
-      if (a_slot[i]) *reinterpret_cast<uint4*>(&sA[buf][a_p[i] * PA + a_c[i] * VEC]) = ra[slot][i][0];
-#pragma unroll
-    for (int i = 0; i < B_PER; ++i)
-      if (b_slot[i]) *reinterpret_cast<uint4*>(&sB[buf][b_p[i] * PB + b_c[i] * VEC]) = rb[slot][i][0];
-  };
-
-  // wave tiles that are multiples of 32 use v_mfma_f32_32x32x16_bf16
-  constexpr bool M32 = WTM % 32 == 0 && WTN % 32 == 0;
-  static_assert(M32, "32x32 wave tiles");
-  constexpr int TM2 = M32 ? WTM / 32 : 1, TN2 = M32 ? WTN / 32 : 1;
-  f32x4_t acc[M32 ? 1 : TM][M32 ? 1 : TN];
-  f32x16_t acc2[TM2][TN2];
-#pragma unroll
-  for (int i = 0; i < (M32 ? 1 : TM); ++i)
-#pragma unroll
-    for (int j = 0; j < (M32 ? 1 : TN); ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc[i][j][q] = 0.f;
-#pragma unroll
-  for (int i = 0; i < TM2; ++i)
-#pragma unroll
-    for (int j = 0; j < TN2; ++j)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) acc2[i][j][q] = 0.f;
-
-  // MFMA fragments straight from the pixel-major tiles with gfx950's
-  // transposing LDS read: in each group of 16 lanes, output e (0..3) of lane i
-  // is element i % 4 of the 8 bytes that lane 4 e + i / 4 of the group
-  // addressed.  A 32x32x16 fragment (lane l: row l % 32, pixels 8 (l / 32) ..
-  // + 8 of the 16-pixel slice) is two such reads: lane j of a group addresses
-  // pixel 8 (l / 32) + j / 4 (+ 4 for the second read), columns
-  // 16 ((l % 32) / 16) + 4 (j % 4) .. + 4 of the wave's 32.
-  const int tr_px = 8 * (lane >> 5) + ((lane & 15) >> 2);
-  const int tr_col = 16 * ((lane & 31) >> 4) + 4 * (lane & 3);
-  auto tr_frag = [&](const T* base, int pitch, int col0, int px0) __attribute__((always_inline)) {
-    typedef short v4i16 __attribute__((ext_vector_type(4)));
-    const T* p = base + (px0 + tr_px) * pitch + col0 + tr_col;
-    const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) v4i16*)(p));
-    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) v4i16*)(p + 4 * pitch));
-    typedef short v8i16 __attribute__((ext_vector_type(8)));
-    const v8i16 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8_t, v);
-  };
-  auto compute = [&](int buf) __attribute__((always_inline)) {
-    const T* A = sA[buf];
-    const T* B = sB[buf];
-#pragma unroll
-    for (int kk = 0; kk < BKm / 16; ++kk) {
-      bf16x8_t af[TM2], bfv[TN2];
-#pragma unroll
-      for (int i = 0; i < TM2; ++i) af[i] = tr_frag(A, PA, wm * WTM + i * 32, kk * 16);
-#pragma unroll
-      for (int j = 0; j < TN2; ++j) bfv[j] = tr_frag(B, PB, wn * WTN + j * 32, kk * 16);
-#pragma unroll
-      for (int i = 0; i < TM2; ++i)
-#pragma unroll
-        for (int j = 0; j < TN2; ++j)
-          acc2[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfv[j], acc2[i][j], 0, 0, 0);
-    }
-  };
-
-  const int nsteps = mend > mbeg ? (mend - mbeg + BKm - 1) / BKm : 0;
-  if (nsteps > 0) {
-    // step j loads into slot j % PF; the last step is re-read past the end
-    static_for<0, PF>([&](auto J) __attribute__((always_inline)) {
-      if (decltype(J)::value >= nsteps) loaded = nsteps - 1;
-      gload(J);
-    });
-    lstore(std::integral_constant<int, 0>{}, 0);
-    __syncthreads();
-    int st0 = 0;
-    for (; st0 + PF <= nsteps; st0 += PF) {
-      static_for<0, PF>([&](auto U) __attribute__((always_inline)) {
-        constexpr int u = decltype(U)::value;
-        const int st = st0 + u;
-        if (st + PF >= nsteps) loaded = nsteps - 1;
-        gload(U);
-        compute(st & 1);
-        if (st + 1 < nsteps) lstore(std::integral_constant<int, (u + 1) % PF>{}, (st + 1) & 1);
-        __syncthreads();
-      });
-    }
-    static_for<0, PF>([&](auto U) __attribute__((always_inline)) {
-      constexpr int u = decltype(U)::value;
-      const int st = st0 + u;
-      if (st < nsteps) {
-        compute(st & 1);
-        if (st + 1 < nsteps) lstore(std::integral_constant<int, (u + 1) % PF>{}, (st + 1) & 1);
-        __syncthreads();
-      }
-    });
-  }
-
-  float* part = (float*)a.part + (size_t)blockIdx.z * N * K;
-  // one split: grad (+)= the tile, the one addition the split reduction
-  // would make; row n goes to its sibling's accumulator when rows are split
-  auto put = [&](int n, int k, float v) __attribute__((always_inline)) {
-    if (n >= N || k >= K) return;
-    if (!a.direct) {
-      part[(size_t)n * K + k] = v;
-      return;
-    }
-    float* g = a.grad;
-    int r = n;
-    for (int j = 0; j < a.nseg; ++j)
-      if (n >= a.seg_row0[j] && n < a.seg_row0[j + 1]) {
-        g = a.seg_grad[j];
-        r = n - a.seg_row0[j];
-      }
-    float* gi = g + (size_t)r * K + k;
-    *gi = (float)((double)*gi + (double)v);  // as the split reduction adds
-  };
-  if constexpr (M32) {
-#pragma unroll
-    for (int i = 0; i < TM2; ++i)
-#pragma unroll
-      for (int j = 0; j < TN2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          put(n0 + wm * WTM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3),
-              k0 + wn * WTN + j * 32 + (lane & 31), acc2[i][j][r]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          put(n0 + wm * WTM + i * 16 + MT<T>::out_row(lane, q), k0 + wn * WTN + j * 16 + (lane & 15),
-              acc[i][j][q]);
-  }
-}
-
 // grad[i] += sum over splits of part[z][i], splits added in order z = 0, 1, ...;
 // each thread owns four consecutive outputs so the partial reads are 16-32 B
 // Destination rows of the weight gradient: one accumulator, or several
@@ -1514,46 +1231,25 @@ hipError_t launch_conv_gemm(int dtype, const ConvArgs& a, hipStream_t s, int* gr
 
 int conv_max_row_tiles(int M) { return (M + 31) / 32; }
 
-// The weight gradient of a filter with 65..96 output channels and K >= 768
-// takes one 96 x 128 tile per K block (all output channels at once, the
-// 32x32x16 form): 3x3 96 -> 96 over 32 x 35 x 35 pixels, 35.9 -> 31.1 us
-// with its split reduction
-static bool wgrad_tile96(int N, int K, int taps) { return N > 64 && N <= 96 && taps > 1 && K >= 768; }
-// A 1x1 filter with 129..192 output channels (the merged 1x1 siblings of an
-// Inception-A module: 176) takes one 192 x 64 tile per K block, about 256
-// workgroups: 256 -> 176 over 32 x 35 x 35 pixels, 28.6 -> 22.5 us with its
-// split reduction
-static bool wgrad_tile192(int N, int taps) { return N > 128 && N <= 192 && taps == 1; }
-
-int wgrad_pick_splits(int dtype, int M, int N, int K, int taps) {
-  // bf16: 64x64 tiles, about 512 workgroups (1x1) or 1024 (larger filters),
-  // from a sweep of the stage shapes; fp32/fp64: the tile of wgrad_dispatch
-  // and about 512 workgroups
+int wgrad_pick_splits(int dtype, int M, int N, int K, int taps, bool lean) {
+  // the general kernels: about 512 workgroups of 64 to 128 rows and columns
+  // (bf16 filters larger than 1x1: 1024)
   const bool bf = dtype == DT_BF16;
-  // bf16, 65..96 output channels of a filter with K >= 768: one 96-row tile
-  // by 128 columns (k_wgrad_t<96,128>), about 512 workgroups
-  const bool t96 = bf && wgrad_tile96(N, K, taps);
-  const bool t192 = bf && !t96 && wgrad_tile192(N, taps);
-  int bm = t96 ? 96 : t192 ? 192 : bf ? 64 : (N <= 64 ? 64 : 128);
-  int bn = t96 ? 128 : bf ? 64 : (K <= 64 ? 64 : 128);
-  int tiles = ((N + bm - 1) / bm) * ((K + bn - 1) / bn);
-  // enough tiles to fill the chip: one split, added straight into the
-  // accumulator (VGG-16's 512 x 4608 gradients at 8 x 8: 72.9 -> 61.5 us)
-  if (bf && tiles >= 512) return 1;
-  int target = t96 ? 512 : t192 ? 256 : bf && taps > 1 ? 1024 : 512;
+  const int bm = bf || N <= 64 ? 64 : 128, bn = bf || K <= 64 ? 64 : 128;
+  const int tiles = ((N + bm - 1) / bm) * ((K + bn - 1) / bn);
+  const int target = bf && taps > 1 ? 1024 : 512;
   int want = (target + tiles - 1) / tiles;
   // at least ~128 pixels per split (VGG-16's 3-channel first layer, one tile:
   // 128 -> 256 splits, 28 -> 20 us with the reduction)
-  int maxs = (M + 127) / 128;
+  const int maxs = (M + 127) / 128;
   // keep the partial sums (written and read back once) below the operands' bytes
-  int64_t op_bytes = (int64_t)M * (N + K / 1) * 2;
-  int64_t part_bytes = (int64_t)N * K * 4;
-  int64_t maxb = part_bytes > 0 ? op_bytes / part_bytes : want;
-  if (maxb < 4) maxb = 4;
-  if (want > maxs) want = maxs;
-  if (want > maxb) want = (int)maxb;
-  if (want < 1) want = 1;
-  return want;
+  const int64_t op_bytes = (int64_t)M * (N + K) * 2, part_bytes = (int64_t)N * K * 4;
+  const int64_t maxb = std::max<int64_t>(4, op_bytes / part_bytes);
+  want = std::max(1, std::min(want, (int)std::min<int64_t>(maxs, maxb)));
+  if (bf && tiles >= 512) want = 1;
+  if (!bf || N % 8 != 0 || K / taps % 8 != 0) return want;
+  const int lds = wgrad_lds_splits(M, N, K, taps);
+  return lean ? std::min(lds, want) : lds;
 }
 size_t wgrad_part_bytes(int dtype, int N, int K, int splits) {
   return (size_t)splits * N * K * (dtype == DT_BF16 ? sizeof(float) : sizeof(double));
@@ -1600,23 +1296,6 @@ static hipError_t wgrad_go(const WgradArgs& a, bool flat, hipStream_t s) {
   return wgrad_reduce<T>(a, s);
 }
 
-template <int BM, int BN, int WM, int WN, int PF, bool GRID = false>
-static hipError_t wgrad_t_go(const WgradArgs& a, hipStream_t s) {
-  int K = a.R * a.S * a.C;
-  dim3 grid((a.N + BM - 1) / BM, (K + BN - 1) / BN, a.splits);
-  const int pix = a.Ho > 0 ? a.Ho * a.Wo : a.H * a.W;
-  double flops = 2.0 * a.nb * pix * (double)a.N * K;
-  static char name[64];
-  snprintf(name, sizeof name, GRID ? "k_wgrad_t<%d,%d,%d,%d,%d,grid>" : "k_wgrad_t<%d,%d,%d,%d,%d>", BM, BN,
-           WM, WN, PF);
-  WgradArgs b = a;
-  b.direct = a.splits == 1;
-  XP_LAUNCH(name, flops, (k_wgrad_t<BM, BN, WM, WN, PF, GRID>), grid, dim3(256), 0, s, b);
-  if (b.direct) return hipGetLastError();
-  return wgrad_reduce<bf16_t>(a, s);
-}
-
-
 template <typename T>
 static hipError_t wgrad_dispatch(const WgradArgs& a, hipStream_t s) {
   constexpr int VEC = MT<T>::VEC;
@@ -1630,14 +1309,10 @@ static hipError_t wgrad_dispatch(const WgradArgs& a, hipStream_t s) {
                         (reinterpret_cast<uintptr_t>(a.dz) % 16) == 0 &&
                         (((size_t)(M - 1)) * a.lddz + a.N) * sizeof(T) < ((size_t)1 << 31) &&
                         (((size_t)(Min - 1)) * a.ldx + a.C) * sizeof(T) < ((size_t)1 << 31);
-    // same grid and square padding: pixel offsets shift with the pixel index;
-    // otherwise each pixel addresses x from its own row and column
-    if (chunks && a.Ho <= 0 && a.pad == a.padw && wgrad_tile96(a.N, K, a.R * a.S))
-      return wgrad_t_go<96, 128, 1, 4, 2>(a, s);
-    if (chunks && a.Ho <= 0 && a.pad == a.padw && wgrad_tile192(a.N, a.R * a.S))
-      return wgrad_t_go<192, 64, 2, 2, 1>(a, s);
-    if (chunks && a.Ho <= 0 && a.pad == a.padw) return wgrad_t_go<64, 64, 2, 2, 1>(a, s);
-    if (chunks) return wgrad_t_go<64, 64, 2, 2, 1, true>(a, s);
+    if (chunks) {
+      const hipError_t e = launch_wgrad_lds(a, s);
+      return e != hipSuccess || a.splits == 1 ? e : wgrad_reduce<T>(a, s);
+    }
   }
   if (n64 && k64) return wgrad_go<T, 64, 64, 2, 2>(a, flat, s);
   if (n64) return wgrad_go<T, 64, 128, 2, 2>(a, flat, s);

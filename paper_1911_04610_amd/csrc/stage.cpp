@@ -100,6 +100,7 @@ struct Op {
   bool valid = false;               // 3x3 stride-2 max pool without padding
   int64_t w_off = -1, b_off = -1;   // parameter offsets (elements)
   int64_t wd_off = -1;              // workspace bytes: flipped weights for the data gradient
+  int splits = 1;                   // weight gradient's pixel splits
   // GEMM over sibling layers that read the same input (merged launch): their
   // weight tensors (parameter offset, output channels) in output-channel order
   std::vector<std::pair<int64_t, int>> segs;
@@ -414,8 +415,8 @@ void plan_lanes(Plan& p) {
   }
 }
 
-xpipe_status build_plan(const xpipe_layer_desc* L, int n, int mb, int H, int W, int C, int dtype,
-                        Plan& p) {
+xpipe_status build_plan_with(const xpipe_layer_desc* L, int n, int mb, int H, int W, int C, int dtype,
+                             bool lean, Plan& p) {
   if (!L || n <= 0) return fail(XPIPE_EINVAL, "empty layer list");
   if (mb <= 0 || H <= 0 || W <= 0 || C <= 0) return fail(XPIPE_EINVAL, "bad input shape");
   if (dtype != DT_F32 && dtype != DT_BF16) return fail(XPIPE_EINVAL, "bad dtype");
@@ -957,8 +958,8 @@ xpipe_status build_plan(const xpipe_layer_desc* L, int n, int mb, int H, int W, 
         op.bnb_part_off = take((size_t)conv_max_row_tiles((int)tin_.sh.rows()) * 2 * op.cin * sizeof(double));
       int M = (int)p.tensors[op.out].sh.rows();  // output pixels (the input's for stride 1)
       int K = op.k * op.kw * op.cin;
-      int splits = wgrad_pick_splits(dtype, M, op.cout, K, op.k * op.kw);
-      wpart = std::max(wpart, wgrad_part_bytes(dtype, op.cout, K, splits));
+      op.splits = wgrad_pick_splits(dtype, M, op.cout, K, op.k * op.kw, lean);
+      wpart = std::max(wpart, wgrad_part_bytes(dtype, op.cout, K, op.splits));
       if (op.b_off >= 0) colpart = std::max(colpart, col_partial_bytes(M, op.cout));
       if (op.stats)
         colpart = std::max(colpart, (size_t)conv_max_row_tiles(M) * 2 * op.cout * sizeof(double));
@@ -993,6 +994,16 @@ xpipe_status build_plan(const xpipe_layer_desc* L, int n, int mb, int H, int W, 
   }
   p.ws = (size_t)align_up((int64_t)off, WS_ALIGN);
   return XPIPE_OK;
+}
+
+// A stage that the static workspace can hold is planned with the leaner pixel
+// splits everywhere, so that it stays within that array and gives the same bits
+// in either kind of workspace.
+xpipe_status build_plan(const xpipe_layer_desc* L, int n, int mb, int H, int W, int C, int dtype, Plan& p) {
+  xpipe_status s = build_plan_with(L, n, mb, H, W, C, dtype, true, p);
+  if (s != XPIPE_OK || p.ws <= XPIPE_STATIC_WORKSPACE_BYTES) return s;
+  p = Plan();
+  return build_plan_with(L, n, mb, H, W, C, dtype, false, p);
 }
 
 // ============================================================================
@@ -1457,7 +1468,6 @@ xpipe_status run_backward(xpipe_stage* st, const Ctx& c, const void* dy, const i
         View g = gradv(st, op.out, c);
         const Tensor& tout = st->tensors[op.out];
         const int M = (int)tout.sh.rows();  // output pixels
-        const int K = op.k * op.kw * op.cin;
         const Op* pool = op.pool_bwd >= 0 ? &st->ops[op.pool_bwd] : nullptr;
         if (pool ? want_grad(pool->in) : want_grad(op.in)) {
           View dx = gradv(st, pool ? pool->in : op.in, c);
@@ -1568,7 +1578,7 @@ xpipe_status run_backward(xpipe_stage* st, const Ctx& c, const void* dy, const i
           w.Ho = tout.sh.H;
           w.Wo = tout.sh.W;
         }
-        w.splits = wgrad_pick_splits(dt, M, op.cout, K, op.k * op.kw);
+        w.splits = op.splits;
         {
           XP_HIP(launch_wgrad(dt, w, s));
         }
