@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 OUT = os.path.join(HERE, "libxpipe.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["k_optim.hip", "k_gemm.hip", "k_conv.hip", "k_wgrad.hip", "k_elem.hip", "stage.cpp"]
+SOURCES = ["k_optim.hip", "k_gemm.hip", "k_conv.hip", "k_wgrad.hip", "k_image.hip", "k_elem.hip", "stage.cpp"]
 ARCH = "gfx950"
 
 

@@ -1224,7 +1224,7 @@ hipError_t launch_conv_gemm(int dtype, const ConvArgs& a, hipStream_t s, int* gr
   if (grid_rows) *grid_rows = 0;
   if (a.nb * a.H * a.W <= 0 || a.N <= 0) return hipSuccess;
   hipError_t e = hipSuccess;
-  if (dtype == DT_BF16 && launch_conv_lds(a, s, grid_rows, &e)) return e;
+  if (dtype == DT_BF16 && (launch_conv_lds(a, s, grid_rows, &e) || launch_conv_image(a, s, grid_rows, &e))) return e;
   return dtype == DT_BF16 ? conv_dispatch<bf16_t>(a, s, grid_rows)
                           : conv_dispatch<float>(a, s, grid_rows);
 }
@@ -1247,6 +1247,9 @@ int wgrad_pick_splits(int dtype, int M, int N, int K, int taps, bool lean) {
   const int64_t maxb = std::max<int64_t>(4, op_bytes / part_bytes);
   want = std::max(1, std::min(want, (int)std::min<int64_t>(maxs, maxb)));
   if (bf && tiles >= 512) want = 1;
+  // images: a workgroup of k_wgrad_image fills a CU (7x7 stride 2, 224x224x3 x 100:
+  // 342 splits of half the workgroup 122 us, 256 of the whole 73 us)
+  if (bf && N % 8 == 0 && K / taps % 8 != 0 && K <= 160) return std::min(want, std::max(1, 256 / ((N + 63) / 64)));
   if (!bf || N % 8 != 0 || K / taps % 8 != 0) return want;
   const int lds = wgrad_lds_splits(M, N, K, taps);
   return lean ? std::min(lds, want) : lds;
@@ -1313,6 +1316,8 @@ static hipError_t wgrad_dispatch(const WgradArgs& a, hipStream_t s) {
       const hipError_t e = launch_wgrad_lds(a, s);
       return e != hipSuccess || a.splits == 1 ? e : wgrad_reduce<T>(a, s);
     }
+    hipError_t e = hipSuccess;
+    if (launch_wgrad_image(a, s, &e)) return e != hipSuccess ? e : wgrad_reduce<T>(a, s);
   }
   if (n64 && k64) return wgrad_go<T, 64, 64, 2, 2>(a, flat, s);
   if (n64) return wgrad_go<T, 64, 128, 2, 2>(a, flat, s);

@@ -1,5 +1,5 @@
 """The tiles and gathers of the bf16 convolution that copies its operands
-straight into LDS (csrc/k_conv.hip), each through a small stage whose sizes
+straight into LDS (csrc/k_conv.hip, k_wgrad.hip), each through a small stage whose sizes
 reach it with a ragged last tile, against the oracle's bf16 model (and the exact
 one where no ReLU is present) at the bf16 bar, 2e-2.
 
@@ -46,6 +46,16 @@ CASES = {
     "few_tiles_one_step": ([conv(-1, 40, 8, 1)], (9, 11, 40), 3),
     "few_tiles_bn_partials": ([conv(-1, 64, 128, 1), bn(0, 128), relu(1), conv(2, 128, 64, 5)], (9, 10, 64), 3),
     "few_tiles_strided": ([conv(-1, 64, 64, 3, stride=2)], (23, 25, 64), 2),
+    # images (csrc/k_image.hip): ragged rows and columns, a second block of
+    # channels, one output row per workgroup, unpadded
+    "image_7x7_s2": ([conv(-1, 3, 64, 7, stride=2), bn(0, 64), relu(1)], (75, 131, 3), 4),
+    "image_7x7_s2_channels_72": ([conv(-1, 3, 72, 7, True, stride=2), relu(0)], (40, 30, 3), 1),
+    "image_3x3": ([conv(-1, 3, 64, 3, True), relu(0)], (32, 32, 3), 3),
+    "image_3x3_odd": ([conv(-1, 3, 24, 3)], (37, 41, 3), 2),
+    "image_3x3_small": ([conv(-1, 3, 32, 3), bn(0, 32)], (5, 3, 3), 2),
+    "image_3x3_s2_unpadded": ([conv(-1, 3, 32, 3, stride=2, pad="valid"), bn(0, 32)], (99, 97, 3), 8),
+    "image_5x5": ([conv(-1, 3, 40, 5)], (33, 70, 3), 60),
+    "image_one_channel": ([conv(-1, 1, 16, 5)], (28, 28, 1), 8),
     # data gradients with mask, accumulation and batch-norm backward partials
     "bn_partials": ([conv(-1, 64, 256, 1), bn(0, 256), relu(1), conv(2, 256, 64, 3), bn(3, 64), conv(2, 256, 72, 1),
                      dict(kind="concat", inputs=[4, 5])], (57, 57, 64), 4),
