@@ -25,6 +25,7 @@
 #include <type_traits>
 #include "xp_kernels.h"
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 
@@ -683,7 +684,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_conv_gemm(ConvArgs a) {
         if (a.accumulate) v += ldd(p);
         std_(p, v);
         if (a.stat_part) {
-          double sv = ldd(p);  // the stored (rounded) value, as the statistics see it
+          const double sv = rnd<T>(v);  // the stored (rounded) value, as the statistics see it
           cs[j] += sv;
           cq[j] += sv * sv;
         }
@@ -1128,6 +1129,18 @@ static int pick_ks_bf16(int C, int taps) {
   return best;
 }
 
+// fp32 storage (16 channels per slice): the depth that pads a tap's channels
+// least, the deepest of those (measured at 24, 48, 96 and 256 channels)
+static int pick_ks_f32(int C) {
+  int best = 1;
+  for (int ks : {2, 4})
+    if ((C + 16 * ks - 1) / (16 * ks) * ks <= (C + 16 * best - 1) / (16 * best) * best) best = ks;
+  return best;
+}
+
+// 64 x 64 tiles of M rows and N columns (at most 1 << 30)
+static int tiles64(int64_t M, int N) { return (int)std::min<int64_t>((M + 63) / 64 * ((N + 63) / 64), 1 << 30); }
+
 template <typename T> static const char* tname() { return sizeof(T) == 2 ? "bf16" : "f32"; }
 
 template <typename T, int BM, int BN, int WM, int WN, bool FLAT, int KS = 0, int PF = 0, int GM = 0>
@@ -1191,10 +1204,13 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
       if (narrow) return conv_go<T, 64, 32, 2, 2, 1, 2, 1>(a, flat, s, gr);
       return conv_go<T, 64, 64, 2, 2, 2, 2, 1>(a, flat, s, gr);
     } else {
+      const int tiles = tiles64((int64_t)a.nb * a.Ho * a.Wo, a.N), ks = flat ? 1 : pick_ks_f32(a.C);
       if (a.tr) {
+        if (tiles < 256 && ks > 1) return conv_go<T, 32, 32, 2, 2, 2, 2, 2>(a, false, s, gr);
         if (narrow) return conv_go<T, 64, 32, 2, 2, 1, 1, 2>(a, flat, s, gr);
         return conv_go<T, 64, 64, 2, 2, 1, 1, 2>(a, flat, s, gr);
       }
+      if (tiles < 256 && ks > 1) return conv_go<T, 32, 32, 2, 2, 2, 2, 1>(a, false, s, gr);
       if (narrow) return conv_go<T, 64, 32, 2, 2, 1, 1, 1>(a, flat, s, gr);
       return conv_go<T, 64, 64, 2, 2, 1, 1, 1>(a, flat, s, gr);
     }
@@ -1215,6 +1231,29 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
     if (ks == 4) return conv_go<T, 32, 64, 2, 2, 4, 2>(a, flat, s, gr);
     return conv_go<T, 32, 64, 2, 2, 2, 2>(a, flat, s, gr);
   } else {
+    // fp32 storage: bound by the f64 MFMA (64 cycles per 16x16x4 product on one
+    // wave) and, with few waves, by the chain of steps on each.  A 64x64 tile gives
+    // a wave four such products per four channels: below four tiles a CU, smaller
+    // tiles and more loads in flight; from there on the 64x64 tile's fewer reads win.
+    // us per launch, 64x64 one step ahead / here, every sum the same chain:
+    //   rows x channels (reduction)   32x256 (256) 16.5 / 8.0    128x2048 (2048) 93 / 31
+    //   1024x256 (3x3x256) 103 / 34   8192x128 (3x3x128) 57 / 52   39200x64 (3x3x128) 133 / 116
+    //   25600x96 (5x5x48) 179 / 143   but 8192x512 (128) 27.4 / 29.4, 39200x128 (3x3x64) 112 / 118
+    const int tiles = tiles64((int64_t)M, a.N);
+    if (flat) {
+      // value-by-value gathers (10 classes: 32x256 (10) 7.0 / 4.4)
+      if (tiles < 256) return conv_go<T, 32, 32, 2, 2, 1, 2>(a, true, s, gr);
+    } else if (tiles < 1024) {
+      const int ks = pick_ks_f32(a.C);
+      // an odd number of 32-channel columns: a 64-wide tile would pad at least a sixth
+      const bool odd = a.N <= 160 && (a.N + 31) / 32 % 2 != 0;
+      if (tiles < 256 || odd) {
+        if (ks == 4) return conv_go<T, 32, 32, 2, 2, 4, 2>(a, false, s, gr);
+        if (ks == 2) return conv_go<T, 32, 32, 2, 2, 2, 2>(a, false, s, gr);
+        return conv_go<T, 32, 32, 2, 2, 1, 2>(a, false, s, gr);
+      }
+      if (ks > 1) return conv_go<T, 32, 64, 2, 2, 2, 2>(a, false, s, gr);
+    }
     if (narrow) return conv_go<T, 64, 32, 2, 2, 1>(a, flat, s, gr);
     return conv_go<T, 64, 64, 2, 2, 1>(a, flat, s, gr);
   }
@@ -1318,6 +1357,18 @@ static hipError_t wgrad_dispatch(const WgradArgs& a, hipStream_t s) {
     }
     hipError_t e = hipSuccess;
     if (launch_wgrad_image(a, s, &e)) return e != hipSuccess ? e : wgrad_reduce<T>(a, s);
+  }
+  if constexpr (sizeof(T) == 4) {
+    // Two 128x128 tiles a CU or fewer leave the f64 MFMA idle behind each wave's own
+    // chain: smaller tiles over the same splits, so the same sums.  us before / here:
+    // 64x64: 512x128 over 8192 pixels 43.0 / 33.6, 128x1152 79 / 59, 2048x2048 over
+    // 128 30.9 / 29.2; 32x32: 256x256 over 32 pixels 10.2 / 3.8, over 392 23.1 / 7.5,
+    // 200x2048 over 128 26.0 / 8.9, 24x360 over 6272 18.0 / 10.6.  With more tiles the
+    // large ones read less (128x576 over 39200, 515 tiles: 128 us, as 64x64 136).
+    const int64_t t64 = (int64_t)tiles64(a.N, K) * a.splits;
+    const int64_t t128 = (int64_t)((a.N + 127) / 128) * ((K + 127) / 128) * a.splits;
+    if (t64 < 256 || (a.N <= 32 && t64 < 512)) return wgrad_go<T, 32, 32, 2, 2>(a, flat, s);
+    if (t128 < 512) return wgrad_go<T, 64, 64, 2, 2>(a, flat, s);
   }
   if (n64 && k64) return wgrad_go<T, 64, 64, 2, 2>(a, flat, s);
   if (n64) return wgrad_go<T, 64, 128, 2, 2>(a, flat, s);

@@ -1,7 +1,8 @@
 """The tiles and gathers of the bf16 convolution that copies its operands
 straight into LDS (csrc/k_conv.hip, k_wgrad.hip), each through a small stage whose sizes
 reach it with a ragged last tile, against the oracle's bf16 model (and the exact
-one where no ReLU is present) at the bf16 bar, 2e-2.
+one where no ReLU is present) at the bf16 bar, 2e-2; and the fp32 tiles of
+csrc/k_gemm.hip against the exact oracle.
 
 A case is picked by rows (micro-batch x H x W), output channels and input
 channels: channels that are no multiple of the 64-channel step take a filter
@@ -80,6 +81,43 @@ def test_conv_tiles_match_oracle(name):
         print(f"{name} vs oracle-{mode}: worst {worst} = {e[worst]:.2e}")
         bad = {k: v for k, v in e.items() if not v <= 2e-2}
         assert not bad, f"vs oracle-{mode}: " + ", ".join(f"{k}={v:.2e}" for k, v in bad.items())
+
+
+# fp32 storage: the general kernel's tiles by the count of 64 x 64 tiles, each with
+# ragged rows and columns; their weight gradients' tiles by workgroups
+F32_CASES = {
+    "32x32_deep": ([conv(-1, 64, 72, 3, True), relu(0)], (7, 9, 64), 3),
+    "32x32_24_channels": ([conv(-1, 24, 40, 7), bn(0, 40)], (9, 11, 24), 3),
+    "32x32_48_channels": ([conv(-1, 48, 20, 5), bn(0, 20)], (9, 11, 48), 3),
+    "32x32_odd_channels": ([conv(-1, 10, 33, 3)], (9, 11, 10), 3),
+    "32x32_odd_columns": ([conv(-1, 64, 96, 1), bn(0, 96)], (65, 64, 64), 4),
+    "32x64": ([conv(-1, 32, 120, 3), bn(0, 120), relu(1)], (47, 45, 32), 4),
+    "64x64": ([conv(-1, 32, 128, 1), bn(0, 128)], (91, 90, 32), 4),
+    "strided": ([conv(-1, 32, 72, 3, stride=2), bn(0, 72)], (23, 25, 32), 2),
+    "strided_1x1": ([conv(-1, 64, 40, 1, stride=2)], (15, 16, 64), 2),
+    "wgrad_64x64": ([conv(-1, 132, 68, 3)], (16, 17, 132), 16),
+    "wgrad_narrow": ([conv(-1, 40, 24, 3)], (14, 14, 40), 32),
+    "linear": ([dict(kind="linear", inputs=[-1], cin=200, cout=72, bias=True), relu(0),
+                dict(kind="linear", inputs=[1], cin=72, cout=10, bias=True)], (200,), 33),
+}
+
+
+@pytest.mark.parametrize("name", list(F32_CASES))
+def test_f32_tiles_match_oracle(name):
+    """Sums are kept in 64 bits and rounded once on store; a chain of at most three
+    stored tensors, each 2^-24 off per value, and batch-norm gradients that subtract
+    means (a factor below 10 here) stay below 1e-5 of the exact oracle."""
+    layers, shape, mb = F32_CASES[name]
+    w = wl.StageWorkload(name, layers, mb, 1, shape, 1, 0, 0, 0, minibatches=1, seed=137)
+    inp = wl.stage_inputs(w, act_dtype="f32")
+    gpu, _ = run_stage(w, inp, xp.F32, xp.Hyper(), 0, 0, minibatches=1)
+    ref = oracle.train_stage(oracle.Stage(layers, "f64"), inp.params, inp.m, inp.v, inp.xs, 0, 0,
+                             oracle.Hyper(), labels=inp.labels, dys=inp.dys)[0]
+    e = _errs(gpu[0], ref)
+    worst = max(e, key=e.get)
+    print(f"{name}: worst {worst} = {e[worst]:.2e}")
+    bad = {k: v for k, v in e.items() if not v <= 1e-5}
+    assert not bad, ", ".join(f"{k}={v:.2e}" for k, v in bad.items())
 
 
 def test_wide_data_gradient_tile():
