@@ -1197,6 +1197,18 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
     // strided or unpadded layers (ResNet-101 stem, first blocks, projections;
     // Inception-V3 stem and grid reductions): general tiles
     if constexpr (sizeof(T) == 2) {
+      // many rows of a channel count that is no multiple of 8: 128-row tiles, or
+      // one 96-column tile for 64 < N <= 96; 10-33% faster there than 64x64
+      if (!flat && !narrow && (int64_t)a.nb * a.Ho * a.Wo >= 65536) {
+        if (a.tr) {
+          if (a.N <= 64) return conv_go<T, 128, 64, 2, 2, 2, 2, 2>(a, false, s, gr);
+          if (a.N <= 96) return conv_go<T, 64, 96, 2, 2, 1, 2, 2>(a, false, s, gr);
+          return conv_go<T, 128, 128, 2, 4, 2, 2, 2>(a, false, s, gr);
+        }
+        if (a.N <= 64) return conv_go<T, 128, 64, 2, 2, 2, 2, 1>(a, false, s, gr);
+        if (a.N <= 96) return conv_go<T, 64, 96, 2, 2, 1, 2, 1>(a, false, s, gr);
+        return conv_go<T, 128, 128, 2, 4, 2, 2, 1>(a, false, s, gr);
+      }
       if (a.tr) {
         if (narrow) return conv_go<T, 64, 32, 2, 2, 1, 2, 2>(a, flat, s, gr);
         return conv_go<T, 64, 64, 2, 2, 2, 2, 2>(a, flat, s, gr);
@@ -1216,8 +1228,9 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
     }
   }
   if constexpr (sizeof(T) == 2) {
-    // What launch_conv_lds leaves: few tiles, odd channel counts or views.
-    // From a sweep on MI355X (tile, stage depth KS, register prefetch depth PF)
+    // What launch_conv_lds leaves: small data gradients, and output channels or
+    // views that are no multiples of 16 bytes, at any size.  From a sweep on MI355X
+    // (tile, stage depth KS, register prefetch depth PF)
     const int taps = a.R * a.S;
     const int ks = flat ? 1 : pick_ks_bf16(a.C, taps);
     // KS counts 32-deep slices for the 16x16 MFMA tiles and 16-deep slices
@@ -1227,7 +1240,25 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
       if (ks == 2) return conv_go<T, 32, 32, 2, 2, 2, 3>(a, flat, s, gr);
       return conv_go<T, 64, 32, 2, 2, 1, 2>(a, flat, s, gr);
     }
+    // many rows: 128-row tiles, 128 columns on eight waves where N allows (1x7 96->507
+    // over 137 376 rows, with its BN and ReLU: 405 us, with 32x64 tiles 447)
+    if (!flat && M >= 65536 && (a.N <= 64 || a.N >= 128)) {
+      if (a.N <= 64) return conv_go<T, 128, 64, 2, 2, 2, 2>(a, false, s, gr);
+      return conv_go<T, 128, 128, 2, 4, 2, 2>(a, false, s, gr);
+    }
+    // one 96-column tile reads the input once and wastes no MFMA columns
+    if (!flat && taps > 1 && taps < 25 && a.N > 64 && a.N <= 96)
+      return conv_go<T, 64, 96, 2, 2, 1, 2>(a, false, s, gr);
     if (ks == 1) return conv_go<T, 64, 64, 2, 2, 2, 2>(a, flat, s, gr);
+    if (!flat && taps == 1 && a.N > 96 && M >= 16384) {
+      // wide 1x1 over many rows: 64-row tiles, the column tile that pads N least
+      if ((a.N + 95) / 96 * 96 <= (a.N + 63) / 64 * 64) return conv_go<T, 64, 96, 2, 2, 1, 2>(a, false, s, gr);
+      return conv_go<T, 64, 64, 2, 2, 2, 2>(a, false, s, gr);
+    }
+    if (taps >= 25 && a.N > 48) {
+      if (ks == 4) return conv_go<T, 64, 64, 2, 2, 8, 2>(a, flat, s, gr);
+      return conv_go<T, 64, 64, 2, 2, 4, 2>(a, flat, s, gr);
+    }
     if (ks == 4) return conv_go<T, 32, 64, 2, 2, 4, 2>(a, flat, s, gr);
     return conv_go<T, 32, 64, 2, 2, 2, 2>(a, flat, s, gr);
   } else {

@@ -47,6 +47,15 @@ CASES = {
     "few_tiles_one_step": ([conv(-1, 40, 8, 1)], (9, 11, 40), 3),
     "few_tiles_bn_partials": ([conv(-1, 64, 128, 1), bn(0, 128), relu(1), conv(2, 128, 64, 5)], (9, 10, 64), 3),
     "few_tiles_strided": ([conv(-1, 64, 64, 3, stride=2)], (23, 25, 64), 2),
+    # output channels that are no multiple of 8: the general kernel's large tiles
+    "general_128x128": ([conv(-1, 32, 132, 1)], (129, 128, 32), 4),
+    "general_128x64": ([conv(-1, 32, 60, 3)], (129, 128, 32), 4),
+    "general_64x96": ([conv(-1, 64, 92, 3)], (27, 29, 64), 4),
+    "general_64x64_1x1": ([conv(-1, 64, 100, 1)], (65, 64, 64), 4),
+    "general_64x64_5x5": ([conv(-1, 128, 68, 5)], (19, 17, 128), 4),
+    "general_strided_128x128": ([conv(-1, 32, 132, 1, stride=2)], (257, 256, 32), 4),
+    "general_strided_128x64": ([conv(-1, 32, 60, 1, stride=2)], (257, 256, 32), 4),
+    "general_strided_64x96": ([conv(-1, 32, 92, 1, stride=2)], (257, 256, 32), 4),
     # images (csrc/k_image.hip): ragged rows and columns, a second block of
     # channels, one output row per workgroup, unpadded
     "image_7x7_s2": ([conv(-1, 3, 64, 7, stride=2), bn(0, 64), relu(1)], (75, 131, 3), 4),
