@@ -29,7 +29,6 @@ static int row_blocks_for(int M, int C) {
 }
 
 int col_row_blocks(int M, int C) { return row_blocks_for(M, C); }
-int col_row_blocks_v(int M, int C, int N);
 // the vectorised reduction uses at most this many row blocks
 constexpr int COL_MAX_ROW_BLOCKS_V = 1024;
 size_t col_partial_bytes(int M, int C) {
@@ -523,12 +522,23 @@ XP_DEV void col_finish_one(const ColArgs& a, int col, double s0, double s1) {
 
 // Block: CL chunk-lanes x RG row groups; partials per (row block, column);
 // the row groups of a block are added in a fixed order in LDS.
+// Bound by the tensors' bytes, and for wide rows by the partials: 8 bytes each, a
+// cache line apart, once per row block and column.  So a block takes at most 32
+// chunks of a row (512 bytes, already whole lines) with the more rows, and about
+// 512 blocks fill the chip.  Batch-norm backward sums in bf16, us per launch with up
+// to 256 chunks and 1024 blocks / here: 1024 columns over 19 600 rows 44 / 20 (4 TB/s;
+// 1024 blocks of 32 chunks 25), 512 over 512 rows 19.7 / 9.0, 256 over 313 600 82 / 74,
+// 64 over 1 254 400 84 / 73.  Two rows per trip with the next trip's loads ahead of the
+// arithmetic gave 1-4% more there, and took 8% where a thread has four rows (96 over
+// 39 200).
+__host__ __device__ static inline int col_lanes(int chunks) { return ceil_div(chunks, ceil_div(chunks, 32)); }
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_colpart_v(ColArgs a) {
   constexpr int N = VT<T>::N;
   __shared__ double sh[2][256][N];
   const int chunks = a.C / N;
-  const int CL = chunks < 256 ? chunks : 256;
+  const int CL = col_lanes(chunks);
   const int RG = 256 / CL;
   const int cl = threadIdx.x % CL, g = threadIdx.x / CL;
   const int chunk = blockIdx.x * CL + cl;
@@ -660,12 +670,11 @@ hipError_t launch_colfinal(const ColArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-int col_row_blocks_v(int M, int C, int N) {
-  int chunks = C / N;
-  int CL = chunks < 256 ? chunks : 256;
+// row blocks of about `blocks` workgroups, each of CL chunks of a row
+static int col_row_blocks_v(int M, int chunks, int CL, int blocks) {
   int RG = 256 / CL;
   int colblocks = ceil_div(chunks, CL);
-  int want = ceil_div(1024, colblocks);         // ~1024 workgroups: every CU busy
+  int want = ceil_div(blocks, colblocks);
   int maxrb = ceil_div(M, RG * 4);              // >= ~4 rows per thread
   if (want > maxrb) want = maxrb;
   if (want > COL_MAX_ROW_BLOCKS_V) want = COL_MAX_ROW_BLOCKS_V;
@@ -676,8 +685,8 @@ template <typename T>
 static hipError_t colreduce_v(ColArgs a, hipStream_t s) {
   constexpr int N = VT<T>::N;
   int chunks = a.C / N;
-  int CL = chunks < 256 ? chunks : 256;
-  a.row_blocks = col_row_blocks_v(a.M, a.C, N);
+  int CL = col_lanes(chunks);
+  a.row_blocks = col_row_blocks_v(a.M, chunks, CL, 512);  // two workgroups a CU (see k_colpart_v)
   XP_LAUNCH(sizeof(T) == 2 ? "k_colpart_v<bf16>" : "k_colpart_v<f32>",
             (double)a.M * a.C * sizeof(T) * (a.mode == COL_BNBWD ? 2 : 1), k_colpart_v<T>,
             dim3(ceil_div(chunks, CL), a.row_blocks), dim3(256), 0, s, a);
@@ -1759,8 +1768,8 @@ hipError_t launch_gap_bwd_bn(int dtype, const PoolArgs& a, const GapBnArgs& b, h
     ok = b.bn_c0[k] % N == 0 && b.bn_c1[k] % N == 0 && b.bn_c0[k] < b.bn_c1[k] && b.bn_c1[k] <= a.C &&
          vec_dt(dtype, rows, a.C, {{b.bn_z[k], b.ld_bnz[k]}});
   if (!ok) return hipErrorInvalidValue;
-  const int rb = col_row_blocks_v((int)rows, a.C, N);
   const int chunks = a.C / N, CL = chunks < 256 ? chunks : 256;
+  const int rb = col_row_blocks_v((int)rows, chunks, CL, 1024);
   const dim3 grid(ceil_div(chunks, CL), rb);
   const double bytes = (double)rows * a.C * (dtype == DT_BF16 ? 2 : 4) * (2 + (a.mask ? 1 : 0) + (a.accumulate ? 1 : 0));
   if (dtype == DT_BF16)

@@ -111,6 +111,38 @@ F32_CASES = {
 }
 
 
+@pytest.mark.parametrize("dtype", [xp.F32, xp.BF16])
+@pytest.mark.parametrize("channels", [8, 264, 1032, 2080])
+@pytest.mark.parametrize("rows", [(1, 3), (5, 7), (61, 67)])
+def test_column_sums(dtype, channels, rows):
+    """Batch-norm sums over columns taken by 1 to 17 workgroups of up to 32 chunks, rows
+    fewer than a block's groups and many trips, against fp64: a batch norm's output
+    is rounded once, its gradients are 64-bit sums rounded once to fp32, of products
+    with the same bf16 or fp32 inputs; dx is one rounding too."""
+    import torch
+    st = xp.Stage([bn(-1, channels)], 2, 1, rows + (channels,), dtype)
+    tdt = torch.bfloat16 if dtype == xp.BF16 else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(5)
+    for off, cnt in st.layout:
+        st.W[off:off + cnt] = 1 + torch.rand(cnt, generator=g, device="cuda")
+    for d in (xp.FWD, xp.BWD):
+        st.xpipe_predict_weights(d, 0, xp.Hyper(), 0)
+    x = (torch.randn(2, *rows, channels, generator=g, device="cuda") + 1).to(tdt)
+    dy = torch.randn(2, *rows, channels, generator=g, device="cuda").to(tdt)
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    st.xpipe_stage_fwd(x, y)
+    st.xpipe_stage_bwd(x, dy, None, dx)
+    X = x.double().reshape(-1, channels).requires_grad_(True)
+    gam, bet = (st.W[off:off + cnt].double().requires_grad_(True) for off, cnt in st.layout)
+    rstd = (X.var(0, unbiased=False) + 1e-5).rsqrt()
+    Y = (X - X.mean(0)) * rstd * gam + bet
+    Y.backward(dy.double().reshape(-1, channels))
+    one = 2.0 ** -8 if dtype == xp.BF16 else 2.0 ** -23
+    for a, b, tol in [(y, Y, one), (dx, X.grad, one)] + [
+            (st.grad[off:off + cnt], p.grad, 2.0 ** -23) for (off, cnt), p in zip(st.layout, (gam, bet))]:
+        assert rel_l2(a.double().cpu().numpy().ravel(), b.detach().cpu().numpy().ravel()) <= tol
+
+
 @pytest.mark.parametrize("name", list(F32_CASES))
 def test_f32_tiles_match_oracle(name):
     """Sums are kept in 64 bits and rounded once on store; a chain of at most three
