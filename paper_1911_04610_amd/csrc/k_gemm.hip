@@ -1305,9 +1305,15 @@ int wgrad_pick_splits(int dtype, int M, int N, int K, int taps, bool lean) {
   // the general kernels: about 512 workgroups of 64 to 128 rows and columns
   // (bf16 filters larger than 1x1: 1024)
   const bool bf = dtype == DT_BF16;
-  const int bm = bf || N <= 64 ? 64 : 128, bn = bf || K <= 64 ? 64 : 128;
+  // channels that are no multiple of 8 and reach k_wgrad's 128x128 tiles: one tile of
+  // 65..96 output channels by 128, about 512 workgroups (1x3 512->73 over 7168
+  // pixels: a step of 357 us, with the 64-wide count's splits 376), or of 129..192
+  // by 64, about 256
+  const bool odd = bf && (N % 8 != 0 || K / taps % 8 != 0) && K > 160;
+  const bool t96 = odd && N > 64 && N <= 96 && taps > 1 && K >= 768, t192 = odd && N > 128 && N <= 192 && taps == 1;
+  const int bm = t96 ? 96 : t192 ? 192 : bf || N <= 64 ? 64 : 128, bn = t96 ? 128 : bf || K <= 64 ? 64 : 128;
   const int tiles = ((N + bm - 1) / bm) * ((K + bn - 1) / bn);
-  const int target = bf && taps > 1 ? 1024 : 512;
+  const int target = t96 ? 512 : t192 ? 256 : bf && taps > 1 ? 1024 : 512;
   int want = (target + tiles - 1) / tiles;
   // at least ~128 pixels per split (VGG-16's 3-channel first layer, one tile:
   // 128 -> 256 splits, 28 -> 20 us with the reduction)

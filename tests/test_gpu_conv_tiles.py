@@ -51,6 +51,8 @@ CASES = {
     "general_128x128": ([conv(-1, 32, 132, 1)], (129, 128, 32), 4),
     "general_128x64": ([conv(-1, 32, 60, 3)], (129, 128, 32), 4),
     "general_64x96": ([conv(-1, 64, 92, 3)], (27, 29, 64), 4),
+    "general_odd_channels": ([conv(-1, 512, 73, 1, kw=3)], (16, 15, 512), 4),
+    "general_odd_channels_1x1": ([conv(-1, 256, 155, 1)], (16, 15, 256), 4),
     "general_64x64_1x1": ([conv(-1, 64, 100, 1)], (65, 64, 64), 4),
     "general_64x64_5x5": ([conv(-1, 128, 68, 5)], (19, 17, 128), 4),
     "general_strided_128x128": ([conv(-1, 32, 132, 1, stride=2)], (257, 256, 32), 4),
