@@ -1301,18 +1301,27 @@ hipError_t launch_conv_gemm(int dtype, const ConvArgs& a, hipStream_t s, int* gr
 
 int conv_max_row_tiles(int M) { return (M + 31) / 32; }
 
-int wgrad_pick_splits(int dtype, int M, int N, int K, int taps, bool lean) {
-  // the general kernels: about 512 workgroups of 64 to 128 rows and columns
-  // (bf16 filters larger than 1x1: 1024)
+// Filters of 65..96 output channels and K >= 768, counted in tiles of 96 x 128, and
+// 1x1 filters of 129..192, in tiles of 192 x 64: where one tile takes all output
+// channels, the 64-wide count's splits are twice to three times as many (1x3 512->73
+// over 7168 pixels: a step of 357 us, with those splits 376)
+static bool wgrad_rows96(int N, int K, int taps) { return N > 64 && N <= 96 && taps > 1 && K >= 768; }
+static bool wgrad_rows192(int N, int taps) { return N > 128 && N <= 192 && taps == 1; }
+
+// A split is one chain of fp32 sums (bf16 storage), and the splits are added in
+// fp64, so their count sets how many bits a gradient keeps: rounding grows with the
+// square root of a chain's length.  512 or 1024 workgroups of 64 x 64 (fp32 storage:
+// of wgrad_dispatch's tile), the fewer for 1x1 filters, whichever kernel takes them.
+// Half as many and longer chains were up to 12 us per launch faster (3x3 256->512
+// over 2048 pixels 28 us with four, 25 with one) with up to twice the error (1.2e-7,
+// 2.5e-7 of the gradient).
+int wgrad_pick_splits(int dtype, int M, int N, int K, int taps) {
   const bool bf = dtype == DT_BF16;
-  // channels that are no multiple of 8 and reach k_wgrad's 128x128 tiles: one tile of
-  // 65..96 output channels by 128, about 512 workgroups (1x3 512->73 over 7168
-  // pixels: a step of 357 us, with the 64-wide count's splits 376), or of 129..192
-  // by 64, about 256
-  const bool odd = bf && (N % 8 != 0 || K / taps % 8 != 0) && K > 160;
-  const bool t96 = odd && N > 64 && N <= 96 && taps > 1 && K >= 768, t192 = odd && N > 128 && N <= 192 && taps == 1;
+  const bool t96 = bf && wgrad_rows96(N, K, taps), t192 = bf && wgrad_rows192(N, taps);
   const int bm = t96 ? 96 : t192 ? 192 : bf || N <= 64 ? 64 : 128, bn = t96 ? 128 : bf || K <= 64 ? 64 : 128;
   const int tiles = ((N + bm - 1) / bm) * ((K + bn - 1) / bn);
+  // enough tiles to fill the chip: one split, added straight into the accumulator
+  if (bf && tiles >= 512) return 1;
   const int target = t96 ? 512 : t192 ? 256 : bf && taps > 1 ? 1024 : 512;
   int want = (target + tiles - 1) / tiles;
   // at least ~128 pixels per split (VGG-16's 3-channel first layer, one tile:
@@ -1322,13 +1331,10 @@ int wgrad_pick_splits(int dtype, int M, int N, int K, int taps, bool lean) {
   const int64_t op_bytes = (int64_t)M * (N + K) * 2, part_bytes = (int64_t)N * K * 4;
   const int64_t maxb = std::max<int64_t>(4, op_bytes / part_bytes);
   want = std::max(1, std::min(want, (int)std::min<int64_t>(maxs, maxb)));
-  if (bf && tiles >= 512) want = 1;
   // images: a workgroup of k_wgrad_image fills a CU (7x7 stride 2, 224x224x3 x 100:
   // 342 splits of half the workgroup 122 us, 256 of the whole 73 us)
   if (bf && N % 8 == 0 && K / taps % 8 != 0 && K <= 160) return std::min(want, std::max(1, 256 / ((N + 63) / 64)));
-  if (!bf || N % 8 != 0 || K / taps % 8 != 0) return want;
-  const int lds = wgrad_lds_splits(M, N, K, taps);
-  return lean ? std::min(lds, want) : lds;
+  return want;
 }
 size_t wgrad_part_bytes(int dtype, int N, int K, int splits) {
   return (size_t)splits * N * K * (dtype == DT_BF16 ? sizeof(float) : sizeof(double));

@@ -6,7 +6,6 @@
 #include "xp_lds.h"
 #include "xp_kernels.h"
 
-#include <algorithm>
 #include <cstdio>
 
 namespace xp {
@@ -256,32 +255,19 @@ hipError_t go(const WgradArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Rows of the tile, from a sweep of the stages' shapes (us per launch with the
-// split reduction, MI355X; the register-staged 64x64, 96x128 and 192x64 tiles
-// before): 128x64 on eight waves for more than 64 channels over many pixels (3x3
-// 256->256 at 14x14x100 38.4, 85.2 before; 1x1 1024->256 there 24.9, 49.6; 3x3
-// 96->96 at 35x35x32 22.5, 30.7; strided 3x3 256->256 at 28x28x100 40.8, 91.7),
-// else 64x64 (3x3 64->64 at 56x56x100 44.7, 112; 3x3 512->512 at 4x4x32 12.0,
-// 22.8, 128x64 12.2; 1x1 512->128 at 16x16x32 11.5, 15.0, 128x64 12.1).
+// Rows of the tile, from a sweep of the stages' shapes over the same splits (us per
+// launch with the split reduction, MI355X; the register-staged 64x64, 96x128 and
+// 192x64 tiles before): 128x64 on eight waves for more than 64 channels from 2048
+// pixels on (3x3 256->256 at 14x14x100 49.4, 64x64 60.4, 91.6 before; 3x3 512->512 at
+// 7x7x100 52.3, 60.2, 123; 3x3 256->512 at 8x8x32 28.0, 30.9, 41.0; 3x3 96->96 at
+// 35x35x32 32.8, 38.9, 34.3; strided 3x3 256->256 at 28x28x100 52.7, 64.9, 95.3; 1x1
+// 1024->512 at 8x8x32 20.9, 21.2, 24.6), else 64x64 (3x3 64->64 at 56x56x100 68, 121;
+// 3x3 512->512 at 4x4x32 17.5, 128x64 17.7, 28.8; 3x3 256->256 there 19.3, 19.8, 22.5;
+// linear 2048->200 over 100 rows 8.7, 9.1, 21.5).
 // 128x128 and 256x128 tiles were 2 to 20% behind, three buffers within 3%.
-int tile_rows(int N, int64_t M) { return N > 64 && M >= 12000 ? 128 : 64; }
+int tile_rows(int N, int64_t M) { return N > 64 && M >= 2048 ? 128 : 64; }
 
 }  // namespace
-
-// Pixel splits: about two workgroups per CU (four for 3x3 and larger filters
-// over very many pixels), each of 512 pixels or more while that leaves one per
-// CU; one split, which needs no reduction, when the tiles nearly fill the chip,
-// or there is little to split.
-int wgrad_lds_splits(int M, int N, int K, int taps) {
-  const int bm = tile_rows(N, M);
-  const int64_t tiles = (int64_t)((N + bm - 1) / bm) * ((K + 63) / 64);
-  if (tiles >= 384 || M <= 256 || (tiles >= 128 && M <= 2048)) return 1;
-  const int64_t target = bm == 64 && taps > 1 && M >= 131072 ? 1024 : 512;
-  int64_t want = std::min(target / tiles, std::max<int64_t>(M / 512, 256 / tiles));
-  // the partial sums (written and read back once) stay below the operands' bytes
-  want = std::min(want, std::max<int64_t>(4, (int64_t)M * (N + K) / (2 * (int64_t)N * K)));
-  return (int)std::max<int64_t>(1, std::min<int64_t>(want, (M + 63) / 64));
-}
 
 hipError_t launch_wgrad_lds(const WgradArgs& a, hipStream_t s) {
   const bool grid = a.Ho > 0 || a.pad != a.padw;

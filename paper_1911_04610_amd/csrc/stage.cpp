@@ -415,8 +415,8 @@ void plan_lanes(Plan& p) {
   }
 }
 
-xpipe_status build_plan_with(const xpipe_layer_desc* L, int n, int mb, int H, int W, int C, int dtype,
-                             bool lean, Plan& p) {
+xpipe_status build_plan(const xpipe_layer_desc* L, int n, int mb, int H, int W, int C, int dtype,
+                        Plan& p) {
   if (!L || n <= 0) return fail(XPIPE_EINVAL, "empty layer list");
   if (mb <= 0 || H <= 0 || W <= 0 || C <= 0) return fail(XPIPE_EINVAL, "bad input shape");
   if (dtype != DT_F32 && dtype != DT_BF16) return fail(XPIPE_EINVAL, "bad dtype");
@@ -958,7 +958,7 @@ xpipe_status build_plan_with(const xpipe_layer_desc* L, int n, int mb, int H, in
         op.bnb_part_off = take((size_t)conv_max_row_tiles((int)tin_.sh.rows()) * 2 * op.cin * sizeof(double));
       int M = (int)p.tensors[op.out].sh.rows();  // output pixels (the input's for stride 1)
       int K = op.k * op.kw * op.cin;
-      op.splits = wgrad_pick_splits(dtype, M, op.cout, K, op.k * op.kw, lean);
+      op.splits = wgrad_pick_splits(dtype, M, op.cout, K, op.k * op.kw);
       wpart = std::max(wpart, wgrad_part_bytes(dtype, op.cout, K, op.splits));
       if (op.b_off >= 0) colpart = std::max(colpart, col_partial_bytes(M, op.cout));
       if (op.stats)
@@ -994,16 +994,6 @@ xpipe_status build_plan_with(const xpipe_layer_desc* L, int n, int mb, int H, in
   }
   p.ws = (size_t)align_up((int64_t)off, WS_ALIGN);
   return XPIPE_OK;
-}
-
-// A stage that the static workspace can hold is planned with the leaner pixel
-// splits everywhere, so that it stays within that array and gives the same bits
-// in either kind of workspace.
-xpipe_status build_plan(const xpipe_layer_desc* L, int n, int mb, int H, int W, int C, int dtype, Plan& p) {
-  xpipe_status s = build_plan_with(L, n, mb, H, W, C, dtype, true, p);
-  if (s != XPIPE_OK || p.ws <= XPIPE_STATIC_WORKSPACE_BYTES) return s;
-  p = Plan();
-  return build_plan_with(L, n, mb, H, W, C, dtype, false, p);
 }
 
 // ============================================================================

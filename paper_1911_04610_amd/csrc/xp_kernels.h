@@ -162,14 +162,11 @@ bool launch_wgrad_image(const WgradArgs& a, hipStream_t s, hipError_t* e);
 // row tiles the forward-type GEMM uses for M rows (upper bound over tile choices)
 int conv_max_row_tiles(int M);
 size_t wgrad_part_bytes(int dtype, int N, int K, int splits);
-// pixel splits of the weight gradient (R*S = taps filter positions); lean: never
-// more partial sums than the general kernels' splits make (a workspace of fixed
-// size)
-int wgrad_pick_splits(int dtype, int M, int N, int K, int taps, bool lean);
+// pixel splits of the weight gradient (R*S = taps filter positions)
+int wgrad_pick_splits(int dtype, int M, int N, int K, int taps);
 // the bf16 kernel that copies its operands straight into LDS (k_wgrad.hip), for
-// 16-byte chunks; and its splits
+// 16-byte chunks
 hipError_t launch_wgrad_lds(const WgradArgs& a, hipStream_t s);
-int wgrad_lds_splits(int M, int N, int K, int taps);
 hipError_t launch_wgrad(int dtype, const WgradArgs& a, hipStream_t s);
 
 // Transposed copies of the convolutions' weights for their data gradients,

@@ -163,6 +163,37 @@ def test_f32_tiles_match_oracle(name):
     assert not bad, ", ".join(f"{k}={v:.2e}" for k, v in bad.items())
 
 
+@pytest.mark.parametrize("view", ["aligned", "odd"])
+@pytest.mark.parametrize("k,kw,cin,cout,hw,mb,chain", [
+    (3, 3, 256, 512, 8, 32, 512), (1, 1, 1024, 512, 8, 32, 512), (3, 3, 256, 256, 4, 32, 128),
+    (3, 3, 256, 256, 14, 32, 832), (7, 1, 160, 192, 12, 100, 768)])
+def test_weight_gradient_chains(k, kw, cin, cout, hw, mb, chain, view):
+    """How many bits a bf16 weight gradient keeps: pixels are summed in chains of
+    `chain`, 16 per fp32 addition, and the chains in fp64.  An addition rounds the
+    sum so far by 0.41 x 2^-24 of it (rms over a binade), a sum of random terms
+    grows with the square root of their count, and so a chain of n additions ends
+    0.41 x 2^-24 sqrt(n / 2) off; 0.6 leaves room for roundings inside an addition.
+    The same where the output gradient starts at an odd 16 bytes (a concat member
+    behind four channels), which takes another kernel."""
+    import torch
+    layers = [conv(-1, cin, cout, k, kw=kw)]
+    if view == "odd":
+        layers = [conv(-1, cin, 4, 1), conv(-1, cin, cout, k, kw=kw), dict(kind="concat", inputs=[0, 1])]
+    st = xp.Stage(layers, mb, 1, (hw, hw, cin), xp.BF16)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(mb, hw, hw, cin, generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randn(st.out_shape, generator=g, device="cuda").to(torch.bfloat16)
+    st.xpipe_predict_weights(xp.BWD, 0, xp.Hyper(), 0)
+    st.xpipe_stage_bwd(x, dy, None, torch.empty_like(x))
+    off, cnt = st.layout[-1]
+    got = st.grad[off:off + cnt].double().reshape(cout, k, kw, cin)
+    d = dy.double()[..., -cout:].reshape(-1, cout).t()
+    xd = torch.nn.functional.pad(x.double(), (0, 0, kw // 2, kw // 2, k // 2, k // 2))
+    ref = torch.stack([torch.stack([d @ xd[:, r:r + hw, q:q + hw].reshape(-1, cin) for q in range(kw)], 1)
+                       for r in range(k)], 1)
+    assert float((got - ref).norm() / ref.norm()) <= 0.6 * 2.0 ** -24 * (chain / 16 / 2) ** 0.5
+
+
 def test_wide_data_gradient_tile():
     """256 x 256 tiles (rows of 256 columns in one workgroup): the masked data
     gradient of a 1 x 1 convolution over 262 160 rows, against fp64 products.
