@@ -1323,18 +1323,14 @@ int wgrad_pick_splits(int dtype, int M, int N, int K, int taps) {
   // enough tiles to fill the chip: one split, added straight into the accumulator
   if (bf && tiles >= 512) return 1;
   const int target = t96 ? 512 : t192 ? 256 : bf && taps > 1 ? 1024 : 512;
-  int want = (target + tiles - 1) / tiles;
+  const int want = (target + tiles - 1) / tiles;
   // at least ~128 pixels per split (VGG-16's 3-channel first layer, one tile:
   // 128 -> 256 splits, 28 -> 20 us with the reduction)
   const int maxs = (M + 127) / 128;
   // keep the partial sums (written and read back once) below the operands' bytes
   const int64_t op_bytes = (int64_t)M * (N + K) * 2, part_bytes = (int64_t)N * K * 4;
   const int64_t maxb = std::max<int64_t>(4, op_bytes / part_bytes);
-  want = std::max(1, std::min(want, (int)std::min<int64_t>(maxs, maxb)));
-  // images: a workgroup of k_wgrad_image fills a CU (7x7 stride 2, 224x224x3 x 100:
-  // 342 splits of half the workgroup 122 us, 256 of the whole 73 us)
-  if (bf && N % 8 == 0 && K / taps % 8 != 0 && K <= 160) return std::min(want, std::max(1, 256 / ((N + 63) / 64)));
-  return want;
+  return std::max(1, std::min(want, (int)std::min<int64_t>(maxs, maxb)));
 }
 size_t wgrad_part_bytes(int dtype, int N, int K, int splits) {
   return (size_t)splits * N * K * (dtype == DT_BF16 ? sizeof(float) : sizeof(double));
@@ -1399,7 +1395,8 @@ static hipError_t wgrad_dispatch(const WgradArgs& a, hipStream_t s) {
       return e != hipSuccess || a.splits == 1 ? e : wgrad_reduce<T>(a, s);
     }
     hipError_t e = hipSuccess;
-    if (launch_wgrad_image(a, s, &e)) return e != hipSuccess ? e : wgrad_reduce<T>(a, s);
+    WgradArgs b = a;
+    if (launch_wgrad_image(a, s, &b.splits, &e)) return e != hipSuccess ? e : wgrad_reduce<T>(b, s);
   }
   if constexpr (sizeof(T) == 4) {
     // Two 128x128 tiles a CU or fewer leave the f64 MFMA idle behind each wave's own

@@ -1,10 +1,11 @@
-// bf16 convolutions of images (a few channels: the networks' first layers) and
-// their weight gradients on CDNA4 MFMA.
+// bf16 convolutions of images (three channels: the networks' first layers), and
+// weight gradients of small filters over channel counts that are no multiple of 8,
+// on CDNA4 MFMA.
 //
-// With few channels a filter row's S x C values are one run of the NHWC row, so a
-// workgroup stages the input rows of several output rows in LDS (zeros around the
-// image) and takes its operands from there value by value: no index arithmetic and
-// no 2-byte load from memory per value, which bound the general kernels.  Bound
+// A filter row's S x C values are one run of the NHWC row, so a workgroup stages
+// the input rows of several output rows in LDS (zeros around the image) and takes
+// its operands from there value by value: no index arithmetic and no 2-byte load
+// from memory per value, which bound the general kernels.  Bound
 // now: one 2-byte LDS read per operand value and the epilogue's fp64 sums, at two
 // waves per SIMD (7x7 stride 2 on 224x224x3, 64 channels, micro-batch 100, before /
 // after: forward 409 / 88 us, weight gradient with its reduction 564 / 80 us; the
@@ -413,6 +414,14 @@ int unit_rows(int64_t images, int Ho, int groups, int idle, int sd, int R, int p
   return best;
 }
 
+// Maps that the weight gradient is for: of `least` output pixels or more, in rows of 8
+// or more.  A workgroup stages each image by itself and waits for it, and computes
+// whole 16-pixel pieces of rows.  us per launch with the reduction, general kernel / this
+// one, 32 images: 1x1 100->200 at 1x1 17 / 71, 4x4 27 / 30, 8x8 and up faster, 3x3 12->64
+// at 7x7 24.5 / 26.9, 10x10 24.4 / 24.0, 3x3 3->64 at 8x8 22.2 / 16.0.
+bool fits_map(int Ho, int Wo, int least) { return Wo >= 8 && (int64_t)Ho * Wo >= least; }
+constexpr int WGRAD_MAP = 64;
+
 template <int R>
 hipError_t conv_go(const ConvArgs& a, int groups, int rb, const Rows& l, int row_blocks, size_t lds, hipStream_t s) {
   static const struct Name {
@@ -452,12 +461,17 @@ bool launch_conv_image(const ConvArgs& a, hipStream_t s, int* row_tiles, hipErro
   return true;
 }
 
-bool launch_wgrad_image(const WgradArgs& a, hipStream_t s, hipError_t* e) {
+bool launch_wgrad_image(const WgradArgs& a0, hipStream_t s, int* splits, hipError_t* e) {
+  WgradArgs a = a0;
   const int Ho = a.Ho > 0 ? a.Ho : a.H, Wo = a.Ho > 0 ? a.Wo : a.W, sd = a.Ho > 0 ? a.stride : 1;
   const int K = a.R * a.S * a.C;
+  if (!fits_map(Ho, Wo, WGRAD_MAP)) return false;
   if (a.C % 8 == 0 || a.ldx != a.C || K > 160 || a.N % 8 != 0 || a.lddz % 8 != 0 || a.nseg > 0 ||
       (reinterpret_cast<uintptr_t>(a.dz) % 16) != 0)
     return false;
+  // a workgroup fills a CU (7x7 stride 2, 224x224x3 x 100: 342 splits of half the
+  // workgroup 122 us, 256 of the whole 73 us)
+  a.splits = std::min(a.splits, std::max(1, 256 / ((a.N + 63) / 64)));
   const Rows l(Wo, 16, sd * a.C, a.S * a.C, a.padw * a.C, a.W * a.C);
   const int rb = unit_rows(a.nb, Ho, a.splits, 2, sd, a.R, l.pitch, WGRAD_ROWS);
   if (rb == 0 || (int64_t)a.H * a.W * a.C >= (1 << 30) || (int64_t)Ho * Wo * a.lddz >= (1 << 30)) return false;
@@ -471,6 +485,7 @@ bool launch_wgrad_image(const WgradArgs& a, hipStream_t s, hipError_t* e) {
     XP_LAUNCH("k_wgrad_image<3>", flops, k_wgrad_image<3>, grid, dim3(512), 0, s, a, rb, l.lead, l.pitch, row_blocks);
   else
     XP_LAUNCH("k_wgrad_image<5>", flops, k_wgrad_image<5>, grid, dim3(512), 0, s, a, rb, l.lead, l.pitch, row_blocks);
+  *splits = a.splits;
   *e = hipGetLastError();
   return true;
 }

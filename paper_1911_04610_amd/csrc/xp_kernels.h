@@ -156,9 +156,9 @@ hipError_t launch_conv_gemm(int dtype, const ConvArgs& a, hipStream_t s, int* gr
 // then nothing is launched; else the launch's status in *e
 bool launch_conv_lds(const ConvArgs& a, hipStream_t s, int* row_tiles, hipError_t* e);
 // the bf16 kernels for images of a few channels (k_image.hip), likewise; the
-// weight gradient leaves its a.splits partials in a.part
+// weight gradient leaves *splits (at most a.splits) partials in a.part
 bool launch_conv_image(const ConvArgs& a, hipStream_t s, int* row_tiles, hipError_t* e);
-bool launch_wgrad_image(const WgradArgs& a, hipStream_t s, hipError_t* e);
+bool launch_wgrad_image(const WgradArgs& a, hipStream_t s, int* splits, hipError_t* e);
 // row tiles the forward-type GEMM uses for M rows (upper bound over tile choices)
 int conv_max_row_tiles(int M);
 size_t wgrad_part_bytes(int dtype, int N, int K, int splits);

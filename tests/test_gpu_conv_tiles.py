@@ -67,6 +67,9 @@ CASES = {
     "image_3x3_small": ([conv(-1, 3, 32, 3), bn(0, 32)], (5, 3, 3), 2),
     "image_3x3_s2_unpadded": ([conv(-1, 3, 32, 3, stride=2, pad="valid"), bn(0, 32)], (99, 97, 3), 8),
     "image_5x5": ([conv(-1, 3, 40, 5)], (33, 70, 3), 60),
+    "image_least_wgrad_map": ([conv(-1, 12, 72, 3)], (8, 8, 12), 5),
+    "image_wgrad_150_channels": ([conv(-1, 150, 88, 1)], (9, 8, 150), 5),
+    "odd_linear": ([dict(kind="linear", inputs=[-1], cin=100, cout=200, bias=True)], (100,), 37),
     "image_one_channel": ([conv(-1, 1, 16, 5)], (28, 28, 1), 8),
     # data gradients with mask, accumulation and batch-norm backward partials
     "bn_partials": ([conv(-1, 64, 256, 1), bn(0, 256), relu(1), conv(2, 256, 64, 3), bn(3, 64), conv(2, 256, 72, 1),
@@ -161,6 +164,41 @@ def test_f32_tiles_match_oracle(name):
     print(f"{name}: worst {worst} = {e[worst]:.2e}")
     bad = {k: v for k, v in e.items() if not v <= 1e-5}
     assert not bad, ", ".join(f"{k}={v:.2e}" for k, v in bad.items())
+
+
+def _launches(st, shape, mb, dtype=xp.BF16):
+    """Launch names of one forward, and of one backward, of a stage."""
+    import torch
+    tdt = torch.bfloat16 if dtype == xp.BF16 else torch.float32
+    x = torch.ones((mb,) + shape, dtype=tdt, device="cuda")
+    dy = torch.ones(st.out_shape, dtype=tdt, device="cuda").reshape((mb, -1) if len(shape) == 1 else st.out_shape)
+    y, dx = torch.empty_like(dy), torch.empty_like(x)
+    for d in (xp.FWD, xp.BWD):
+        st.xpipe_predict_weights(d, 0, xp.Hyper(), 0)
+    out = []
+    for run in (lambda: st.xpipe_stage_fwd(x, y), lambda: st.xpipe_stage_bwd(x, dy, None, dx)):
+        st.set_timing(True)
+        run()
+        torch.cuda.synchronize()
+        out.append(list(st.timing()))
+        st.set_timing(False)
+    return out
+
+
+LINEAR = dict(kind="linear", inputs=[-1], cin=100, cout=200, bias=False)
+
+
+@pytest.mark.parametrize("layer,shape,mb,wgrad", [
+    (LINEAR, (100,), 128, "k_wgrad<"),  # behind a global pool: 128 maps of one pixel
+    (conv(-1, 12, 64, 1), (7, 7, 12), 32, "k_wgrad<"),
+    (conv(-1, 12, 64, 1), (8, 8, 12), 32, "k_wgrad_image<"),
+    (conv(-1, 3, 64, 3), (7, 9, 3), 8, "k_wgrad<"),
+    (conv(-1, 3, 64, 3), (12, 12, 3), 8, "k_wgrad_image<"),
+    (conv(-1, 3, 64, 3), (200, 7, 3), 4, "k_wgrad<")])
+def test_image_weight_gradient_takes_images(layer, shape, mb, wgrad):
+    """A map of a few pixels keeps the general kernel, which batches over images."""
+    _, b = _launches(xp.Stage([layer], mb, 1, shape, xp.BF16), shape, mb)
+    assert any(n.startswith(wgrad) for n in b), b
 
 
 @pytest.mark.parametrize("view", ["aligned", "odd"])
