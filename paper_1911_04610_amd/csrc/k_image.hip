@@ -414,13 +414,15 @@ int unit_rows(int64_t images, int Ho, int groups, int idle, int sd, int R, int p
   return best;
 }
 
-// Maps that the weight gradient is for: of `least` output pixels or more, in rows of 8
-// or more.  A workgroup stages each image by itself and waits for it, and computes
-// whole 16-pixel pieces of rows.  us per launch with the reduction, general kernel / this
-// one, 32 images: 1x1 100->200 at 1x1 17 / 71, 4x4 27 / 30, 8x8 and up faster, 3x3 12->64
-// at 7x7 24.5 / 26.9, 10x10 24.4 / 24.0, 3x3 3->64 at 8x8 22.2 / 16.0.
+// Maps that the kernels are for: of `least` output pixels or more, in rows of 8 or
+// more.  A workgroup stages each image by itself and waits for it, and computes whole
+// 16- or 32-pixel pieces of rows.  us per launch, general kernels / these: forward 3x3
+// 3->64, 64 images, of 2x2 10.3 / 31, 6x6 11.1 / 15.1, 10x10 11.0 / 11.9, 12x12 10.9 / 10.4,
+// 16x16 11.2 / 8.5, 4 images of 200x4 11.1 / 12.3; weight gradients with their
+// reduction, 32 images, of 1x1 100->200 at 1x1 17 / 71, 4x4 27 / 30, 8x8 and up faster, 3x3
+// 12->64 at 7x7 24.5 / 26.9, 10x10 24.4 / 24.0, 3x3 3->64 at 8x8 22.2 / 16.0.
 bool fits_map(int Ho, int Wo, int least) { return Wo >= 8 && (int64_t)Ho * Wo >= least; }
-constexpr int WGRAD_MAP = 64;
+constexpr int CONV_MAP = 144, WGRAD_MAP = 64;
 
 template <int R>
 hipError_t conv_go(const ConvArgs& a, int groups, int rb, const Rows& l, int row_blocks, size_t lds, hipStream_t s) {
@@ -442,6 +444,7 @@ hipError_t conv_go(const ConvArgs& a, int groups, int rb, const Rows& l, int row
 bool launch_conv_image(const ConvArgs& a, hipStream_t s, int* row_tiles, hipError_t* e) {
   const int Ho = a.Ho > 0 ? a.Ho : a.H, Wo = a.Ho > 0 ? a.Wo : a.W, sd = a.Ho > 0 ? a.stride : 1;
   // forward, square filters, images without row gaps, 16-byte chunks of the output
+  if (!fits_map(Ho, Wo, CONV_MAP)) return false;
   if (a.C != 3 || a.R != a.S || (a.R != 3 && a.R != 5 && a.R != 7) || a.ldx != 3 || a.tr || a.mask || a.accumulate ||
       a.bn_part || a.N % 8 != 0 || a.ldy % 8 != 0 || (reinterpret_cast<uintptr_t>(a.y) % 16) != 0)
     return false;

@@ -67,6 +67,8 @@ CASES = {
     "image_3x3_small": ([conv(-1, 3, 32, 3), bn(0, 32)], (5, 3, 3), 2),
     "image_3x3_s2_unpadded": ([conv(-1, 3, 32, 3, stride=2, pad="valid"), bn(0, 32)], (99, 97, 3), 8),
     "image_5x5": ([conv(-1, 3, 40, 5)], (33, 70, 3), 60),
+    "image_least_map": ([conv(-1, 3, 40, 5, True), relu(0)], (12, 12, 3), 3),
+    "image_least_map_s2": ([conv(-1, 3, 72, 7, stride=2), bn(0, 72)], (35, 15, 3), 3),
     "image_least_wgrad_map": ([conv(-1, 12, 72, 3)], (8, 8, 12), 5),
     "image_wgrad_150_channels": ([conv(-1, 150, 88, 1)], (9, 8, 150), 5),
     "odd_linear": ([dict(kind="linear", inputs=[-1], cin=100, cout=200, bias=True)], (100,), 37),
@@ -188,16 +190,20 @@ def _launches(st, shape, mb, dtype=xp.BF16):
 LINEAR = dict(kind="linear", inputs=[-1], cin=100, cout=200, bias=False)
 
 
-@pytest.mark.parametrize("layer,shape,mb,wgrad", [
-    (LINEAR, (100,), 128, "k_wgrad<"),  # behind a global pool: 128 maps of one pixel
-    (conv(-1, 12, 64, 1), (7, 7, 12), 32, "k_wgrad<"),
-    (conv(-1, 12, 64, 1), (8, 8, 12), 32, "k_wgrad_image<"),
-    (conv(-1, 3, 64, 3), (7, 9, 3), 8, "k_wgrad<"),
-    (conv(-1, 3, 64, 3), (12, 12, 3), 8, "k_wgrad_image<"),
-    (conv(-1, 3, 64, 3), (200, 7, 3), 4, "k_wgrad<")])
-def test_image_weight_gradient_takes_images(layer, shape, mb, wgrad):
-    """A map of a few pixels keeps the general kernel, which batches over images."""
-    _, b = _launches(xp.Stage([layer], mb, 1, shape, xp.BF16), shape, mb)
+@pytest.mark.parametrize("layer,shape,mb,fwd,wgrad", [
+    (LINEAR, (100,), 128, "k_conv_gemm<", "k_wgrad<"),  # behind a global pool: 128 maps of one pixel
+    (conv(-1, 12, 64, 1), (7, 7, 12), 32, "k_conv_gemm<", "k_wgrad<"),
+    (conv(-1, 12, 64, 1), (8, 8, 12), 32, "k_conv_gemm<", "k_wgrad_image<"),
+    (conv(-1, 3, 64, 3), (7, 9, 3), 8, "k_conv_gemm<", "k_wgrad<"),
+    (conv(-1, 3, 64, 3), (11, 13, 3), 8, "k_conv_gemm<", "k_wgrad_image<"),
+    (conv(-1, 3, 64, 3), (12, 12, 3), 8, "k_conv_gemm_image<", "k_wgrad_image<"),
+    (conv(-1, 3, 64, 7, stride=2), (23, 24, 3), 8, "k_conv_gemm_image<", "k_wgrad_image<"),
+    (conv(-1, 3, 64, 5, pad="valid"), (12, 12, 3), 8, "k_conv_gemm<", "k_wgrad_image<"),
+    (conv(-1, 3, 64, 3), (200, 7, 3), 4, "k_conv_gemm<", "k_wgrad<")])
+def test_image_kernels_take_images(layer, shape, mb, fwd, wgrad):
+    """A map of a few pixels keeps the general kernels, which batch over images."""
+    f, b = _launches(xp.Stage([layer], mb, 1, shape, xp.BF16), shape, mb)
+    assert any(n.startswith(fwd) for n in f), f
     assert any(n.startswith(wgrad) for n in b), b
 
 
