@@ -308,15 +308,17 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
   const bool live_n = n < a.N;
   bf16_t* y = (bf16_t*)a.y;
   const bf16_t* mask = (const bf16_t*)a.mask;
-  // mean and 1 / deviation of the batch norm that column tid belongs to
-  double col_mean = 0.0, col_rstd = 0.0;
+  // of the batch norm that column tid belongs to: 1 / deviation (0 for a bias's columns,
+  // which have the first sum only, and for columns of neither, which have no sums)
+  double col_rstd = 0.0;
+  bool col_sum = false;
   if (DG && a.bn_part && tid < BN && n0 + tid < a.N) {
     const int c = n0 + tid;
 #pragma unroll
     for (int q = 0; q < CONV_BN_SEGS; ++q)
-      if (q < a.bn_nseg && c >= a.bn_c0[q] && c < a.bn_c1[q] && a.bn_z[q]) {
-        col_mean = a.bn_mean[q][c - a.bn_c0[q]];
-        col_rstd = a.bn_rstd[q][c - a.bn_c0[q]];
+      if (q < a.bn_nseg && c >= a.bn_c0[q] && c < a.bn_c1[q]) {
+        col_sum = true;
+        if (a.bn_z[q]) col_rstd = a.bn_rstd[q][c - a.bn_c0[q]];
       }
   }
   // output pixel of the lane's chunk of pass p in strip t, or -1
@@ -330,18 +332,19 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
     return m;
   };
   const int n_in = live_n ? n : 0;
-  // input of the batch norm whose output gradient these columns are (else any
-  // readable chunk, whose sums are not kept)
+  // input and means of the batch norm whose output gradient these columns are (else
+  // any readable chunk, whose sums are not kept)
   const bf16_t* z = (const bf16_t*)a.x;
   int ldz = 0;
-  bool has_z = false;
+  double mean[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   if (DG && a.bn_part && live_n) {
 #pragma unroll
     for (int q = 0; q < CONV_BN_SEGS; ++q)
       if (q < a.bn_nseg && n >= a.bn_c0[q] && n < a.bn_c1[q] && a.bn_z[q]) {
         z = (const bf16_t*)a.bn_z[q] + (n - a.bn_c0[q]);
         ldz = a.ld_bnz[q];
-        has_z = true;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mean[e] = a.bn_mean[q][n - a.bn_c0[q] + e];
       }
   }
   // a data gradient's operands in 16-byte chunks: mask, earlier contribution,
@@ -441,7 +444,7 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
     // 16-byte chunks, so the fp32 strip goes through LDS and a lane finishes
     // chunks of one chunk column.
     float* ot = reinterpret_cast<float*>(st0) + (FEW ? 0 : wave) * (SR * WTN);
-    double v[16];  // column sums: of g, then of g z
+    double v[16];  // column sums: of g, then of g (z - mean)
 #pragma unroll
     for (int e = 0; e < 16; ++e) v[e] = 0.0;
 #pragma unroll
@@ -489,10 +492,10 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
             // the stored gradient, as what reads it sees it
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-              const uint32_t w = pr[e >> 1], zw = has_z ? c_z[p][e >> 1] : 0u;
+              const uint32_t w = pr[e >> 1], zw = c_z[p][e >> 1];
               const double g = (double)__uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
               v[e] += g;
-              v[8 + e] += g * (double)__uint_as_float((e & 1) ? (zw & 0xffff0000u) : (zw << 16));
+              v[8 + e] += g * ((double)__uint_as_float((e & 1) ? (zw & 0xffff0000u) : (zw << 16)) - mean[e]);
             }
           }
         }
@@ -528,10 +531,10 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
       s0 += sred[w][0][tid];
       s1 += sred[w][1][tid];
     }
-    // sum of g (z - mean) rstd from the sums of g z and g: the products are
-    // exact in fp64, and a bf16 z bounds what the difference can cancel
-    // (mean / deviation below 2^9); a bias's columns have no z, second sum 0
-    if (DG) s1 = (s1 - col_mean * s0) * col_rstd;
+    if (DG) {
+      s0 = col_sum ? s0 : 0.0;
+      s1 = col_rstd != 0.0 ? s1 * col_rstd : 0.0;
+    }
     part[((size_t)(n0 + tid) * 2 + 0) * tiles_m + tm] = s0;
     part[((size_t)(n0 + tid) * 2 + 1) * tiles_m + tm] = s1;
   }

@@ -238,6 +238,42 @@ def test_weight_gradient_chains(k, kw, cin, cout, hw, mb, chain, view):
     assert float((got - ref).norm() / ref.norm()) <= 0.6 * 2.0 ** -24 * (chain / 16 / 2) ** 0.5
 
 
+def test_bn_partials_of_near_constant_channels():
+    """A channel whose values are equal but in a few rows, its mean 2^7 to 2^14 times
+    its deviation: the sum of g (z - mean) rstd that a data gradient's epilogue takes.
+    The identity filter makes g the output gradient exactly.  A 64-bit sum centred
+    before it is formed, stored in fp32: 2^-23 of it."""
+    import torch
+    c, mb, hw = 64, 4, 91
+    st = xp.Stage([bn(-1, c), relu(0), conv(1, c, c, 1)], mb, 1, (hw, hw, c), xp.BF16)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    x = (2.0 ** torch.arange(c, device="cuda").remainder(12)).expand(mb, hw, hw, c).clone()
+    rows = x.view(-1, c)
+    for k in range(c):  # one to 64 rows one unit in the last place up
+        at = torch.randint(0, rows.shape[0], (1 + k,), generator=g, device="cuda")
+        rows[at, k] *= 1 + 2.0 ** -7
+    x = x.to(torch.bfloat16)
+    (go, gn), (bo, bc), (wo, wn) = st.layout
+    st.W[go:go + gn] = 1.0
+    st.W[bo:bo + bc] = 1.0  # every output positive
+    st.W[wo:wo + wn] = torch.eye(c, device="cuda").reshape(-1)
+    for d in (xp.FWD, xp.BWD):
+        st.xpipe_predict_weights(d, 0, xp.Hyper(), 0)
+    dy = torch.randn(mb, hw, hw, c, generator=g, device="cuda").to(torch.bfloat16)
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    st.xpipe_stage_fwd(x, y)
+    st.set_timing(True)
+    st.xpipe_stage_bwd(x, dy, None, dx)
+    torch.cuda.synchronize()
+    assert any(n.startswith("k_conv_gemm_lds<128,64,4,2,64,2,false,0,true") for n in st.timing()), list(st.timing())
+    X, G = x.double().reshape(-1, c), dy.double().reshape(-1, c)
+    xhat = (X - X.mean(0)) * (X.var(0, unbiased=False) + 1e-5).rsqrt()
+    ref = (G * xhat).sum(0)
+    assert float(((st.grad[go:go + gn].double() - ref) / ref).abs().max()) <= 2.0 ** -23
+    ref = G.sum(0)
+    assert float(((st.grad[bo:bo + bc].double() - ref) / ref).abs().max()) <= 2.0 ** -23
+
+
 def test_wide_data_gradient_tile():
     """256 x 256 tiles (rows of 256 columns in one workgroup): the masked data
     gradient of a 1 x 1 convolution over 262 160 rows, against fp64 products.
