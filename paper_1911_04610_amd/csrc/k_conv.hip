@@ -569,6 +569,9 @@ bool chunks16(const void* p, int ld) { return (reinterpret_cast<uintptr_t>(p) % 
 
 int64_t tiles(int64_t rows, int bm, int cols, int bn) { return ((rows + bm - 1) / bm) * ((cols + bn - 1) / bn); }
 
+// 128-column tiles pad N by at most an eighth more than 64-column ones
+bool fits128(int N) { return 8 * ((N + 127) / 128 * 128) <= 9 * ((N + 63) / 64 * 64); }
+
 // Tile by size, from a sweep of the stages' shapes (us per launch, MI355X):
 //  - up to 32 columns 128x32, up to 64 128x64 (3x3 64->64 at 56x56x100: 46.5,
 //    64x64 tiles 52.5), 65..96 96x96 (3x3 64->96 at 35x35x32: 14.6; 64x128
@@ -586,9 +589,9 @@ int64_t tiles(int64_t rows, int bm, int cols, int bn) { return ((rows + bm - 1) 
 // Two buffers: a third or fourth lost more workgroups per CU than it hid.
 template <bool RAG, int GM, bool DG>
 hipError_t pick_tile(const ConvArgs& a, int64_t rows, hipStream_t s, int* row_tiles) {
-  if (a.N <= 32) return go<128, 32, 4, 1, 64, 2, RAG, GM, DG>(a, s, row_tiles);
-  const int64_t pad64 = (a.N + 63) / 64 * 64, pad128 = (a.N + 127) / 128 * 128;
-  if (a.N > 96 && 8 * pad128 <= 9 * pad64) {
+  if constexpr (!DG || GM == 2)
+    if (a.N <= 32) return go<128, 32, 4, 1, 64, 2, RAG, GM, DG>(a, s, row_tiles);
+  if (a.N > 96 && fits128(a.N)) {
     if constexpr (DG && GM == 0)
       if (a.N % 256 == 0 && tiles(rows, 256, a.N, 256) >= 1024)
         return go<256, 256, 2, 4, 64, 2, RAG, GM, DG>(a, s, row_tiles);
@@ -649,34 +652,62 @@ bool launch_conv_lds(const ConvArgs& a, hipStream_t s, int* row_tiles, hipError_
   if (!fits || (grid && dg && !a.tr)) return false;
   ConvArgs b = a;
   b.stride = stride;
+  // Which calls the general kernel does faster, from a sweep of 1x1 to 5x5, strided and
+  // unpadded layers over 8 to 512 columns, reductions of 8 to 12800 and 512 to 100 352
+  // rows (us per launch, general kernel / here; a data gradient with mask and
+  // batch-norm partials).  Both form the same sums.
   const int64_t K = (int64_t)a.R * a.S * a.C;
   const int cols = a.N <= 32 ? 32 : 64;
-  if (dg && !a.tr) {
-    // small data gradients, where the epilogue counts for more than the loop,
-    // stay with the general kernel (1x1 256->512 at 14x14x8: 6.8, here 8.8 us; 1x1
-    // 256->512 at 14x14x16: 9.2 / 9.8; 3x3 128->128 at 16x16x32: 12.0 / 12.8; 3x3 64->64
-    // at 28x28x16: 8.4 / 10.1) unless the reduction is long (1x1 1024->256 at
-    // 14x14x32: 20.0 / 15.0; 3x3 256->256 at 14x14x16: 18.6 / 17.5; 3x3
-    // 512->512 at 4x4x32: 21.5 / 19.4)
-    const bool wide = a.N > 96;
-    const bool many = wide ? tiles(rows, 128, a.N, 128) >= 192 : tiles(rows, 128, a.N, cols) >= 256;
-    if (!many) {
-      if (wide && K >= 1024 && tiles(rows, 64, a.N, 128) >= 192) {
-      } else if (K >= 2048 && tiles(rows, 64, a.N, cols) >= 192) {
-      } else if (K >= 4096 && tiles(rows, 64, a.N, cols) < 192) {
-        *e = few<0, true>(b, s, row_tiles);
-        return true;
-      } else {
-        return false;
-      }
+  const bool w96 = a.N > 64 && a.N <= 96, tile128 = a.N > 96 && fits128(a.N) && tiles(rows, 128, a.N, 128) >= 192;
+  const int64_t t64 = tiles(rows, 64, a.N, cols);
+  if (a.tr) {
+    // The residue classes leave a product a quarter of the steps, so a short one is all
+    // epilogue: 1x1 stride 2, 32 columns of 16 at 12 544 rows 7.8 / 11.2, 64 of 128 10.5 /
+    // 11.5, 128 of 64 at 19 600 rows 13.3 / 16.0; from 512 on 0.6 to 0.9 of its time, 32
+    // columns from 1025 on 0.5 to 0.8.
+    if (a.N <= 32 ? K <= 1024 : K <= 256 && (!tile128 || K <= 32)) return false;
+  } else if (dg) {
+    // A data gradient's epilogue counts for more than the loop where the reduction is
+    // short, or 32-row tiles spread it better: 32 columns of 64 at 50 176 rows 10.1 / 13.7,
+    // of 4608 at 12 544 rows 26.5 / 40.8; 96 of 32 at 25 088 rows 12.3 / 16.3.  Its 64x96
+    // tile takes 3x3 filters (96 of 576 at 25 088 rows 19.3 / 22.0), not 1x1 or 5x5 ones
+    // (96 of 512 0.55 to 0.87 of its time here, 96 of 2400 0.7).
+    if (K < 64 || (K < 128 && a.C % 64 != 0) || a.N <= 32) return false;
+    const int taps = a.R * a.S;
+    if (a.N > 96 ? tiles(rows, 128, a.N, 128) >= 192 : tiles(rows, 128, a.N, 64) >= 256) {
+      if (w96 && K < (taps == 1 || taps >= 25 ? 256 : 1024)) return false;
+    } else if (a.N > 96 && K >= 1024 && tiles(rows, 64, a.N, 128) >= 192) {
+      // (1x1 1024->256 at 14x14x32: 20.0 / 15.0)
+    } else if (K >= 2048 && t64 >= (w96 ? 192 : 256)) {
+      // (64 of 2304, 196 tiles 20.8 / 25.7; 307 tiles 0.96, 452 0.78 of its time)
+    } else if (K >= 4096 && t64 <= (w96 ? 192 : 64)) {
+      // (3x3 512->512 at 4x4x32: 21.5 / 19.4; 128 of 4608, 154 tiles 30 / 40)
+      *e = few<0, true>(b, s, row_tiles);
+      return true;
+    } else {
+      return false;  // (1x1 256->512 at 14x14x16: 9.2 / 9.8; 3x3 64->64 at 28x28x16: 8.4 / 10.1)
     }
-  } else if (!a.tr && tiles(rows, 64, a.N, cols) < 192 && (K > 256 || tiles(rows, 64, a.N, cols) < 96)) {
+  } else if (t64 < 192 && (K > 256 || t64 < 96)) {
     // fewer 64x64 tiles than CUs (two or four steps: not far fewer, 1x1 128->512
-    // over 1000 rows, 128 tiles: 4.5 against 4.8 us; a data gradient by residue
-    // classes keeps them: 3x3 stride 2, 256->256 at 14x14x8, 14.1 / 15.7)
+    // over 1000 rows, 128 tiles: 4.5 against 4.8 us)
     if (grid) *e = few<1, false>(b, s, row_tiles);
     else *e = few<0, false>(b, s, row_tiles);
     return true;
+  } else if (a.N <= 32) {
+    // one column tile, so rows / 128 workgroups: below one per CU the smaller tiles are
+    // better (3x3 256->32 at 14 700 rows 15.6 / 21.5, few's 14.2); a short reduction hides
+    // less (1x1 32->32 at 100 352 rows 9.1 / 11.1); and where the input exceeds the L2s'
+    // 32 MB its rows come from further away for every filter tap (3x3 256->32 there 54 /
+    // 77, 128->32 0.85 of its time)
+    if (K <= 288 || (!grid && a.C > 128 && rows * a.C > 18000000)) return false;
+    if (!grid && rows < 24576) {
+      *e = few<0, false>(b, s, row_tiles);
+      return true;
+    }
+  } else if ((K <= 32 && !(w96 && tiles(rows, 128, a.N, 64) >= 512)) || (K >= 3584 && !grid && t64 < 256)) {
+    // a step of mostly zeros (1x1 32->256 at 12 544 rows 7.8 / 9.0); 192 to 255 tiles of
+    // long chains (3x3 512->64 at 12 544 rows 30 / 36)
+    return false;
   }
   if (a.tr) *e = pick_step<2, true>(b, rows, s, row_tiles);
   else if (grid) *e = pick_step<1, false>(b, rows, s, row_tiles);

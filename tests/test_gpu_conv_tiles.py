@@ -207,6 +207,32 @@ def test_image_kernels_take_images(layer, shape, mb, fwd, wgrad):
     assert any(n.startswith(wgrad) for n in b), b
 
 
+def _lds(names, dg):
+    """Tiles of the LDS-copy forwards (dg false) or data gradients among launch names."""
+    args = [n[len("k_conv_gemm_lds<"):-1].split(",") for n in names if n.startswith("k_conv_gemm_lds<")]
+    return ["x".join(a[:2]) for a in args if a[8] == ("true" if dg else "false")]
+
+
+@pytest.mark.parametrize("k,cin,cout,hw,mb,stride,dg,tile", [
+    # data gradients of up to 32 channels, of short reductions, of 3x3 filters into 65..96
+    # channels and of 196 tiles: the general kernel
+    (1, 32, 512, 91, 4, 1, True, None), (1, 64, 32, 91, 4, 1, True, None), (1, 64, 64, 91, 4, 1, True, "128x64"),
+    (1, 96, 192, 91, 4, 1, True, None), (1, 96, 256, 91, 4, 1, True, "96x96"),
+    (3, 96, 96, 91, 4, 1, True, None), (3, 64, 256, 56, 4, 1, True, None), (3, 64, 256, 64, 4, 1, True, "64x64"),
+    (3, 128, 512, 28, 4, 1, True, None), (3, 64, 512, 28, 4, 1, True, "32x32"),
+    # by residue classes: from 257 products on, up to 32 channels from 1025
+    (1, 64, 256, 40, 4, 2, True, None), (1, 64, 264, 40, 4, 2, True, "64x64"), (3, 32, 112, 40, 4, 2, True, None),
+    (3, 32, 120, 40, 4, 2, True, "128x32"), (1, 128, 64, 91, 4, 2, True, "128x128"), (1, 128, 32, 91, 4, 2, True, None),
+    # forwards of up to 32 channels, of at most 32 products, of 196 tiles with long chains
+    (1, 288, 32, 91, 4, 1, False, None), (3, 40, 32, 91, 4, 1, False, "128x32"), (3, 64, 32, 60, 4, 1, False, "32x32"),
+    (1, 32, 256, 91, 4, 1, False, None), (1, 40, 256, 91, 4, 1, False, "128x128"),
+    (3, 400, 64, 56, 4, 1, False, None), (3, 392, 64, 56, 4, 1, False, "64x64")])
+def test_lds_copy_kernel_takes_what_it_does_faster(k, cin, cout, hw, mb, stride, dg, tile):
+    layers = [bn(-1, cin), relu(0), conv(1, cin, cout, k, stride=stride)]
+    f, b = _launches(xp.Stage(layers, mb, 1, (hw, hw, cin), xp.BF16), (hw, hw, cin), mb)
+    assert _lds(b if dg else f, dg) == ([] if tile is None else [tile]), (f, b)
+
+
 @pytest.mark.parametrize("view", ["aligned", "odd"])
 @pytest.mark.parametrize("k,kw,cin,cout,hw,mb,chain", [
     (3, 3, 256, 512, 8, 32, 512), (1, 1, 1024, 512, 8, 32, 512), (3, 3, 256, 256, 4, 32, 128),
