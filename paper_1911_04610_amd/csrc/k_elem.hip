@@ -686,7 +686,12 @@ static hipError_t colreduce_v(ColArgs a, hipStream_t s) {
   constexpr int N = VT<T>::N;
   int chunks = a.C / N;
   int CL = col_lanes(chunks);
-  a.row_blocks = col_row_blocks_v(a.M, chunks, CL, 512);  // two workgroups a CU (see k_colpart_v)
+  // two workgroups a CU (see k_colpart_v); four where two fp32 tensors of 64 MB or more
+  // come from memory (backward sums, us, with 512 / 1024: 64 columns over 313 600 rows 44
+  // / 33, 96 there 65 / 49, 320 over 78 400 56 / 43; 512 over 78 400 83 / 84, and bf16 as
+  // above)
+  const bool far = sizeof(T) == 4 && a.mode == COL_BNBWD && a.C <= 320 && (int64_t)a.M * a.C >= 16000000;
+  a.row_blocks = col_row_blocks_v(a.M, chunks, CL, far ? 1024 : 512);
   XP_LAUNCH(sizeof(T) == 2 ? "k_colpart_v<bf16>" : "k_colpart_v<f32>",
             (double)a.M * a.C * sizeof(T) * (a.mode == COL_BNBWD ? 2 : 1), k_colpart_v<T>,
             dim3(ceil_div(chunks, CL), a.row_blocks), dim3(256), 0, s, a);

@@ -150,6 +150,12 @@ def test_column_sums(dtype, channels, rows):
         assert rel_l2(a.double().cpu().numpy().ravel(), b.detach().cpu().numpy().ravel()) <= tol
 
 
+@pytest.mark.parametrize("channels", [64, 264])
+def test_column_sums_of_many_f32_rows(channels):
+    """16 million values and more in fp32: twice the workgroups."""
+    test_column_sums(xp.F32, channels, (181, 4 * 64 * 182 // channels))
+
+
 @pytest.mark.parametrize("name", list(F32_CASES))
 def test_f32_tiles_match_oracle(name):
     """Sums are kept in 64 bits and rounded once on store; a chain of at most three
