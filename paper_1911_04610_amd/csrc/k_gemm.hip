@@ -1271,13 +1271,18 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
     //   1024x256 (3x3x256) 103 / 34   8192x128 (3x3x128) 57 / 52   39200x64 (3x3x128) 133 / 116
     //   25600x96 (5x5x48) 179 / 143   but 8192x512 (128) 27.4 / 29.4, 39200x128 (3x3x64) 112 / 118
     const int tiles = tiles64((int64_t)M, a.N);
+    // up to 32 columns, where 32-row tiles are as many rounds of half the work as 64-row
+    // ones are: the 64x32 tile's fewer reads win (3x3 16->32 over 441 64-row tiles 1.04,
+    // 691 1.03, 919 1.06 of its time with 32x32, but 383 0.87, 613 0.89; flat, over 129 to
+    // 256 1.05 to 1.08), unless the steps of 32x32 are deeper (256 channels 0.92)
+    const bool even = narrow && (tiles + 127) / 128 % 2 == 0;
     if (flat) {
       // value-by-value gathers (10 classes: 32x256 (10) 7.0 / 4.4)
-      if (tiles < 256) return conv_go<T, 32, 32, 2, 2, 1, 2>(a, true, s, gr);
+      if (tiles < 256 && !even) return conv_go<T, 32, 32, 2, 2, 1, 2>(a, true, s, gr);
     } else if (tiles < 1024) {
       const int ks = pick_ks_f32(a.C);
       // an odd number of 32-channel columns: a 64-wide tile would pad at least a sixth
-      const bool odd = a.N <= 160 && (a.N + 31) / 32 % 2 != 0;
+      const bool odd = a.N <= 160 && (a.N + 31) / 32 % 2 != 0 && !(even && ks < 4);
       if (tiles < 256 || odd) {
         if (ks == 4) return conv_go<T, 32, 32, 2, 2, 4, 2>(a, false, s, gr);
         if (ks == 2) return conv_go<T, 32, 32, 2, 2, 2, 2>(a, false, s, gr);

@@ -239,6 +239,16 @@ def test_lds_copy_kernel_takes_what_it_does_faster(k, cin, cout, hw, mb, stride,
     assert _lds(b if dg else f, dg) == ([] if tile is None else [tile]), (f, b)
 
 
+@pytest.mark.parametrize("cin,rows64,tile", [
+    (16, 200, "32,32"), (16, 300, "32,32"), (16, 469, "64,32"), (64, 469, "32,32"), (16, 600, "32,32"), (16, 700, "64,32"),
+    (10, 120, "32,32"), (10, 200, "64,32"), (10, 300, "64,32")])
+def test_f32_narrow_tiles(cin, rows64, tile):
+    """Up to 32 columns in fp32 storage: 32-row tiles where they shorten the last round."""
+    shape = (8, rows64, cin)
+    f, _ = _launches(xp.Stage([conv(-1, cin, 32, 1)], 8, 1, shape, xp.F32), shape, 8, xp.F32)
+    assert any(n.startswith(f"k_conv_gemm<f32,{tile},") for n in f), f
+
+
 @pytest.mark.parametrize("view", ["aligned", "odd"])
 @pytest.mark.parametrize("k,kw,cin,cout,hw,mb,chain", [
     (3, 3, 256, 512, 8, 32, 512), (1, 1, 1024, 512, 8, 32, 512), (3, 3, 256, 256, 4, 32, 128),
