@@ -1370,7 +1370,7 @@ __global__ __launch_bounds__(256) void k_gap_bwd_bn_v(PoolArgs a, GapBnArgs b, i
   constexpr int N = VT<T>::N;
   __shared__ double sh[2][256][N];
   const int chunks = a.C / N;
-  const int CL = chunks < 256 ? chunks : 256;
+  const int CL = col_lanes(chunks);
   const int RG = 256 / CL;
   const int cl = threadIdx.x % CL, g = threadIdx.x / CL;
   const int chunk = blockIdx.x * CL + cl;
@@ -1773,8 +1773,11 @@ hipError_t launch_gap_bwd_bn(int dtype, const PoolArgs& a, const GapBnArgs& b, h
     ok = b.bn_c0[k] % N == 0 && b.bn_c1[k] % N == 0 && b.bn_c0[k] < b.bn_c1[k] && b.bn_c1[k] <= a.C &&
          vec_dt(dtype, rows, a.C, {{b.bn_z[k], b.ld_bnz[k]}});
   if (!ok) return hipErrorInvalidValue;
-  const int chunks = a.C / N, CL = chunks < 256 ? chunks : 256;
-  const int rb = col_row_blocks_v((int)rows, chunks, CL, 1024);
+  // split as k_colpart_v, for the same reasons (bf16, us with up to 256 chunks and 1024
+  // workgroups / here: 2048 columns over 4900 rows 70 / 22, 512 over 19 600 31 / 23, 256
+  // over 122 500 52 / 49)
+  const int chunks = a.C / N, CL = col_lanes(chunks);
+  const int rb = col_row_blocks_v((int)rows, chunks, CL, 512);
   const dim3 grid(ceil_div(chunks, CL), rb);
   const double bytes = (double)rows * a.C * (dtype == DT_BF16 ? 2 : 4) * (2 + (a.mask ? 1 : 0) + (a.accumulate ? 1 : 0));
   if (dtype == DT_BF16)

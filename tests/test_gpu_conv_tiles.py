@@ -150,6 +150,33 @@ def test_column_sums(dtype, channels, rows):
         assert rel_l2(a.double().cpu().numpy().ravel(), b.detach().cpu().numpy().ravel()) <= tol
 
 
+@pytest.mark.parametrize("channels", [8, 264, 1032, 2080])
+@pytest.mark.parametrize("hw", [(1, 2), (4, 8), (32, 64)])
+def test_column_sums_of_the_pool_gradient(channels, hw):
+    """The same sums taken by the global average pool's backward.  A power of two of
+    pixels makes its gradient exact; 64-bit sums stored in fp32."""
+    import torch
+    st = xp.Stage([bn(-1, channels), relu(0), dict(kind="gap", inputs=[1])], 3, 1, hw + (channels,), xp.BF16)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    (go, gn), (bo, bc) = st.layout
+    st.W[go:go + gn] = 1 + torch.rand(channels, generator=g, device="cuda")
+    st.W[bo:bo + bc] = torch.randn(channels, generator=g, device="cuda")
+    for d in (xp.FWD, xp.BWD):
+        st.xpipe_predict_weights(d, 0, xp.Hyper(), 0)
+    x = (torch.randn(3, *hw, channels, generator=g, device="cuda") + 1).to(torch.bfloat16)
+    dy = torch.randn(3, 1, 1, channels, generator=g, device="cuda").to(torch.bfloat16)
+    st.set_timing(True)
+    st.xpipe_stage_bwd(x, dy, None, torch.empty_like(x))
+    torch.cuda.synchronize()
+    assert "k_gap_bwd_bn_v<bf16>" in st.timing(), list(st.timing())
+    X = x.double().reshape(-1, channels)
+    xhat = (X - X.mean(0)) * (X.var(0, unbiased=False) + 1e-5).rsqrt()
+    z = xhat * st.W[go:go + gn].double() + st.W[bo:bo + bc].double()
+    G = (dy.double() / (hw[0] * hw[1])).expand(3, *hw, channels).reshape(-1, channels) * (z > 0)
+    for off, cnt, ref in ((go, gn, (G * xhat).sum(0)), (bo, bc, G.sum(0))):
+        assert rel_l2(st.grad[off:off + cnt].double().cpu().numpy(), ref.cpu().numpy()) <= 2.0 ** -23
+
+
 @pytest.mark.parametrize("channels", [64, 264])
 def test_column_sums_of_many_f32_rows(channels):
     """16 million values and more in fp32: twice the workgroups."""
