@@ -1396,8 +1396,10 @@ static hipError_t wgrad_dispatch(const WgradArgs& a, hipStream_t s) {
                         (((size_t)(M - 1)) * a.lddz + a.N) * sizeof(T) < ((size_t)1 << 31) &&
                         (((size_t)(Min - 1)) * a.ldx + a.C) * sizeof(T) < ((size_t)1 << 31);
     if (chunks) {
-      const hipError_t e = launch_wgrad_lds(a, s);
-      return e != hipSuccess || a.splits == 1 ? e : wgrad_reduce<T>(a, s);
+      WgradArgs b = a;
+      b.splits = wgrad_lds_splits(M, a.splits);
+      const hipError_t e = launch_wgrad_lds(b, s);
+      return e != hipSuccess || b.splits == 1 ? e : wgrad_reduce<T>(b, s);
     }
     hipError_t e = hipSuccess;
     WgradArgs b = a;

@@ -165,8 +165,9 @@ size_t wgrad_part_bytes(int dtype, int N, int K, int splits);
 // pixel splits of the weight gradient (R*S = taps filter positions)
 int wgrad_pick_splits(int dtype, int M, int N, int K, int taps);
 // the bf16 kernel that copies its operands straight into LDS (k_wgrad.hip), for
-// 16-byte chunks
+// 16-byte chunks; and those of the plan's splits that it uses (the first ones)
 hipError_t launch_wgrad_lds(const WgradArgs& a, hipStream_t s);
+int wgrad_lds_splits(int M, int splits);
 hipError_t launch_wgrad(int dtype, const WgradArgs& a, hipStream_t s);
 
 // Transposed copies of the convolutions' weights for their data gradients,

@@ -279,7 +279,8 @@ def test_f32_narrow_tiles(cin, rows64, tile):
 @pytest.mark.parametrize("view", ["aligned", "odd"])
 @pytest.mark.parametrize("k,kw,cin,cout,hw,mb,chain", [
     (3, 3, 256, 512, 8, 32, 512), (1, 1, 1024, 512, 8, 32, 512), (3, 3, 256, 256, 4, 32, 128),
-    (3, 3, 256, 256, 14, 32, 832), (7, 1, 160, 192, 12, 100, 768)])
+    (3, 3, 256, 256, 14, 32, 832), (7, 1, 160, 192, 12, 100, 768),
+    (3, 3, 96, 96, 35, 32, 576)])  # 69 of the 74 planned chains hold pixels
 def test_weight_gradient_chains(k, kw, cin, cout, hw, mb, chain, view):
     """How many bits a bf16 weight gradient keeps: pixels are summed in chains of
     `chain`, 16 per fp32 addition, and the chains in fp64.  An addition rounds the
