@@ -1288,7 +1288,7 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
         if (ks == 2) return conv_go<T, 32, 32, 2, 2, 2, 2>(a, false, s, gr);
         return conv_go<T, 32, 32, 2, 2, 1, 2>(a, false, s, gr);
       }
-      if (ks > 1) return conv_go<T, 32, 64, 2, 2, 2, 2>(a, false, s, gr);
+      if (ks > 1 && !narrow) return conv_go<T, 32, 64, 2, 2, 2, 2>(a, false, s, gr);
     }
     if (narrow) return conv_go<T, 64, 32, 2, 2, 1>(a, flat, s, gr);
     return conv_go<T, 64, 64, 2, 2, 1>(a, flat, s, gr);

@@ -267,7 +267,7 @@ def test_lds_copy_kernel_takes_what_it_does_faster(k, cin, cout, hw, mb, stride,
 
 
 @pytest.mark.parametrize("cin,rows64,tile", [
-    (16, 200, "32,32"), (16, 300, "32,32"), (16, 469, "64,32"), (64, 469, "32,32"), (16, 600, "32,32"), (16, 700, "64,32"),
+    (16, 200, "32,32"), (16, 300, "32,32"), (16, 469, "64,32"), (32, 469, "64,32"), (64, 469, "32,32"), (16, 600, "32,32"), (16, 700, "64,32"),
     (10, 120, "32,32"), (10, 200, "64,32"), (10, 300, "64,32")])
 def test_f32_narrow_tiles(cin, rows64, tile):
     """Up to 32 columns in fp32 storage: 32-row tiles where they shorten the last round."""
