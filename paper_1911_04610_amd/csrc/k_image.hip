@@ -418,11 +418,13 @@ int unit_rows(int64_t images, int Ho, int groups, int idle, int sd, int R, int p
 // more.  A workgroup stages each image by itself and waits for it, and computes whole
 // 16- or 32-pixel pieces of rows.  us per launch, general kernels / these: forward 3x3
 // 3->64, 64 images, of 2x2 10.3 / 31, 6x6 11.1 / 15.1, 10x10 11.0 / 11.9, 12x12 10.9 / 10.4,
-// 16x16 11.2 / 8.5, 4 images of 200x4 11.1 / 12.3; weight gradients with their
-// reduction, 32 images, of 1x1 100->200 at 1x1 17 / 71, 4x4 27 / 30, 8x8 and up faster, 3x3
-// 12->64 at 7x7 24.5 / 26.9, 10x10 24.4 / 24.0, 3x3 3->64 at 8x8 22.2 / 16.0.
+// 16x16 11.2 / 8.5, 4 images of 200x4 11.1 / 12.3, and 3->32, whose general tile pads
+// less, of 12x12 9.7 / 10.2, 15x16 10.1 / 8.8; weight gradients with their reduction, 32
+// images, of 1x1 100->200 at 1x1 17 / 71, 4x4 27 / 30, 3x3 12->64 at 7x7 24.5 / 26.9, 3x3
+// 3->64 at 8x8 22.2 / 16.0, and of more than 96 products, five tiles a wave, 5x5 6->64 at
+// 11x11 24.3 / 27.1, at 16x16 25.5 / 21.4.
 bool fits_map(int Ho, int Wo, int least) { return Wo >= 8 && (int64_t)Ho * Wo >= least; }
-constexpr int CONV_MAP = 144, WGRAD_MAP = 64;
+constexpr int CONV_MAP = 144, CONV_MAP_NARROW = 240, WGRAD_MAP = 64, WGRAD_MAP_WIDE = 144;
 
 template <int R>
 hipError_t conv_go(const ConvArgs& a, int groups, int rb, const Rows& l, int row_blocks, size_t lds, hipStream_t s) {
@@ -444,7 +446,7 @@ hipError_t conv_go(const ConvArgs& a, int groups, int rb, const Rows& l, int row
 bool launch_conv_image(const ConvArgs& a, hipStream_t s, int* row_tiles, hipError_t* e) {
   const int Ho = a.Ho > 0 ? a.Ho : a.H, Wo = a.Ho > 0 ? a.Wo : a.W, sd = a.Ho > 0 ? a.stride : 1;
   // forward, square filters, images without row gaps, 16-byte chunks of the output
-  if (!fits_map(Ho, Wo, CONV_MAP)) return false;
+  if (!fits_map(Ho, Wo, a.N <= 32 ? CONV_MAP_NARROW : CONV_MAP)) return false;
   if (a.C != 3 || a.R != a.S || (a.R != 3 && a.R != 5 && a.R != 7) || a.ldx != 3 || a.tr || a.mask || a.accumulate ||
       a.bn_part || a.N % 8 != 0 || a.ldy % 8 != 0 || (reinterpret_cast<uintptr_t>(a.y) % 16) != 0)
     return false;
@@ -468,7 +470,11 @@ bool launch_wgrad_image(const WgradArgs& a0, hipStream_t s, int* splits, hipErro
   WgradArgs a = a0;
   const int Ho = a.Ho > 0 ? a.Ho : a.H, Wo = a.Ho > 0 ? a.Wo : a.W, sd = a.Ho > 0 ? a.stride : 1;
   const int K = a.R * a.S * a.C;
-  if (!fits_map(Ho, Wo, WGRAD_MAP)) return false;
+  if (!fits_map(Ho, Wo, K > 96 ? WGRAD_MAP_WIDE : WGRAD_MAP)) return false;
+  // strided 1x1 filters read a quarter of the staged values; with many channels, in rows
+  // that go through registers, the staging is the time (stride 2, 32 images of 46x46,
+  // general kernel / here: 150->128 42 / 76 us, 60->128, whose rows are copied, 25 / 21)
+  if (a.R < sd && a.C > 48 && a.W * a.C % 8 != 0) return false;
   if (a.C % 8 == 0 || a.ldx != a.C || K > 160 || a.N % 8 != 0 || a.lddz % 8 != 0 || a.nseg > 0 ||
       (reinterpret_cast<uintptr_t>(a.dz) % 16) != 0)
     return false;

@@ -70,7 +70,8 @@ CASES = {
     "image_least_map": ([conv(-1, 3, 40, 5, True), relu(0)], (12, 12, 3), 3),
     "image_least_map_s2": ([conv(-1, 3, 72, 7, stride=2), bn(0, 72)], (35, 15, 3), 3),
     "image_least_wgrad_map": ([conv(-1, 12, 72, 3)], (8, 8, 12), 5),
-    "image_wgrad_150_channels": ([conv(-1, 150, 88, 1)], (9, 8, 150), 5),
+    "image_wgrad_150_channels": ([conv(-1, 150, 88, 1)], (13, 12, 150), 5),
+    "image_wgrad_44_channels_s2": ([conv(-1, 44, 24, 1, stride=2)], (17, 15, 44), 5),
     "odd_linear": ([dict(kind="linear", inputs=[-1], cin=100, cout=200, bias=True)], (100,), 37),
     "image_one_channel": ([conv(-1, 1, 16, 5)], (28, 28, 1), 8),
     # data gradients with mask, accumulation and batch-norm backward partials
@@ -232,6 +233,10 @@ LINEAR = dict(kind="linear", inputs=[-1], cin=100, cout=200, bias=False)
     (conv(-1, 3, 64, 3), (12, 12, 3), 8, "k_conv_gemm_image<", "k_wgrad_image<"),
     (conv(-1, 3, 64, 7, stride=2), (23, 24, 3), 8, "k_conv_gemm_image<", "k_wgrad_image<"),
     (conv(-1, 3, 64, 5, pad="valid"), (12, 12, 3), 8, "k_conv_gemm<", "k_wgrad_image<"),
+    (conv(-1, 3, 32, 3), (15, 15, 3), 8, "k_conv_gemm<", "k_wgrad_image<"),
+    (conv(-1, 3, 32, 3), (15, 16, 3), 8, "k_conv_gemm_image<", "k_wgrad_image<"),
+    (conv(-1, 3, 64, 7), (11, 13, 3), 8, "k_conv_gemm<", "k_wgrad<"),
+    (conv(-1, 111, 16, 1, stride=2), (35, 31, 111), 8, "k_conv_gemm<", "k_wgrad<"),
     (conv(-1, 3, 64, 3), (200, 7, 3), 4, "k_conv_gemm<", "k_wgrad<")])
 def test_image_kernels_take_images(layer, shape, mb, fwd, wgrad):
     """A map of a few pixels keeps the general kernels, which batch over images."""
