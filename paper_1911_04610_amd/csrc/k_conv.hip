@@ -35,7 +35,7 @@ namespace {
 // FEW (few tiles, a long reduction): a 32 x 32 tile whose four waves hold 16 x 16
 // results each (16x16x32 MFMA), with more steps in flight; one wave finishes
 // the tile.  Every element is still one chain of sums in channel order.
-template <int BM, int BN, int WM, int WN, int BK, int NS, bool RAG, int GM, bool DG, bool FEW, int UF>
+template <int BM, int BN, int WM, int WN, int BK, int NS, bool RAG, int GM, bool DG, bool FEW>
 __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(ConvArgs a, int tiles_m) {
   constexpr int NW = FEW ? 4 : WM * WN;
   static_assert(!FEW || (WM * WN == 1 && BM == 32 && BN == 32 && BK == 64), "four 16 x 16 waves");
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
 
   if (nk > 0) {
     // steps are copied and multiplied U at a time, one barrier each
-    constexpr int U = FEW ? UF : 1;
+    constexpr int U = FEW ? 2 : 1;
     static_assert(NS % U == 0 && NS >= 2 * U, "whole groups of buffers");
     static_for<0, NS - U>([&](auto I) __attribute__((always_inline)) { copy(I); });
     int k = 0;
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(FEW ? 256 : WM * WN * 64) void k_conv_gemm_lds(Conv
   }
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int NS, bool RAG, int GM, bool DG = GM == 2, bool FEW = false, int UF = 1>
+template <int BM, int BN, int WM, int WN, int BK, int NS, bool RAG, int GM, bool DG = GM == 2, bool FEW = false>
 hipError_t go(const ConvArgs& a, hipStream_t s, int* row_tiles) {
   int tiles = 0;
   if (GM == 2) {
@@ -560,7 +560,7 @@ hipError_t go(const ConvArgs& a, hipStream_t s, int* row_tiles) {
                RAG ? "true" : "false", GM, DG ? "true" : "false", FEW ? "true" : "false");
     }
   } name;
-  XP_LAUNCH(name.s, flops, (k_conv_gemm_lds<BM, BN, WM, WN, BK, NS, RAG, GM, DG, FEW, UF>),
+  XP_LAUNCH(name.s, flops, (k_conv_gemm_lds<BM, BN, WM, WN, BK, NS, RAG, GM, DG, FEW>),
             dim3(tiles * ((a.N + BN - 1) / BN)), dim3(FEW ? 256 : WM * WN * 64), 0, s, a, tiles);
   return hipGetLastError();
 }
@@ -624,9 +624,9 @@ hipError_t pick_step(const ConvArgs& a, int64_t rows, hipStream_t s, int* row_ti
 // first of these, but other bits flip ReLU and pool decisions downstream.
 template <int GM, bool DG>
 hipError_t few(const ConvArgs& a, hipStream_t s, int* row_tiles) {
-  if (a.C % 64 != 0) return go<32, 32, 1, 1, 64, 4, true, GM, DG, true, 2>(a, s, row_tiles);
-  if ((int64_t)a.R * a.S * a.C >= 4096) return go<32, 32, 1, 1, 64, 8, false, GM, DG, true, 2>(a, s, row_tiles);
-  return go<32, 32, 1, 1, 64, 4, false, GM, DG, true, 2>(a, s, row_tiles);
+  if (a.C % 64 != 0) return go<32, 32, 1, 1, 64, 4, true, GM, DG, true>(a, s, row_tiles);
+  if ((int64_t)a.R * a.S * a.C >= 4096) return go<32, 32, 1, 1, 64, 8, false, GM, DG, true>(a, s, row_tiles);
+  return go<32, 32, 1, 1, 64, 4, false, GM, DG, true>(a, s, row_tiles);
 }
 
 }  // namespace

@@ -12,43 +12,36 @@ namespace xp {
 
 namespace {
 
-// LDS tiles hold one row per pixel, WID (32, 64 or 128) elements wide, without
-// padding: the 16-byte chunk c of row p sits at position c ^ swz(p), which
+// LDS tiles hold one row per pixel, WID (64 or 128) elements wide, without padding: the 16-byte chunk c of row p sits at position c ^ swz(p), which
 // moves four consecutive rows (what 16 lanes of a transposing read touch) to
 // different 64-byte bank groups.  swz is the same for all rows that a lane
 // copies, and for all that it reads.
 template <int WID>
 XP_DEV int swz(int row) {
-  return WID == 128 ? (row & 3) << 2 : WID == 64 ? ((row >> 1) & 1) << 2 : 0;
+  static_assert(WID == 64 || WID == 128, "tile width");
+  return WID == 128 ? (row & 3) << 2 : ((row >> 1) & 1) << 2;
 }
 
 // One workgroup per BM x BN tile (output channels x reduction chunks) and pixel
-// split, WM x WN waves of 32x32x16 MFMA tiles, BP pixels per step, NS buffers.
+// split, WM x WN waves of 32x32x16 MFMA tiles, BP pixels per step, two buffers.
 // The reduction runs over pixels, which are the rows of both operands in
 // memory, so the fragments (8 consecutive pixels of one column per lane) are
 // read with the transposing LDS read.  GRID: strided or unpadded convolutions
 // (dz lives on the Ho x Wo grid).
-template <int BM, int BN, int WM, int WN, int BP, int NS, bool GRID>
+template <int BM, int BN, int WM, int WN, int BP, bool GRID>
 __global__ __launch_bounds__(WM * WN * 64) void k_wgrad_lds(WgradArgs a, int tiles_n, int tiles_k) {
   constexpr int NW = WM * WN;
   constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
   static_assert(WTM % 32 == 0 && WTN % 32 == 0 && BP % 16 == 0, "wave tile");
-  constexpr int AW = BM > 128 ? 128 : BM, NA = BM / AW;  // A: NA tiles AW wide
-  static_assert(BN <= 128, "one chunk column per lane");
-  constexpr int ACPR = AW / 8, ARPI = 64 / ACPR, BCPR = BN / 8, BRPI = 64 / BCPR;
-  constexpr int A_T = NA * (BP / ARPI), B_T = BP / BRPI;  // copy instructions per step
+  constexpr int ACPR = BM / 8, ARPI = 64 / ACPR, BCPR = BN / 8, BRPI = 64 / BCPR;
+  constexpr int A_T = BP / ARPI, B_T = BP / BRPI;  // copy instructions per step
   constexpr int A_I = (A_T + NW - 1) / NW, B_I = (B_T + NW - 1) / NW;
-  constexpr int LOADS = A_I + B_I;
   constexpr int SZ = BP * (BM + BN);
   __shared__ __align__(16) bf16_t st0[SZ];
   __shared__ __align__(16) bf16_t st1[SZ];
-  __shared__ __align__(16) bf16_t st2[NS > 2 ? SZ : 8];
-  static_assert(NS == 2 || NS == 3, "stages");
   auto stage = [&](auto I) __attribute__((always_inline)) -> bf16_t* {
-    constexpr int i = decltype(I)::value;
-    if constexpr (i == 0) return st0;
-    else if constexpr (i == 1) return st1;
-    else return st2;
+    if constexpr (decltype(I)::value == 0) return st0;
+    else return st1;
   };
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -75,9 +68,8 @@ __global__ __launch_bounds__(WM * WN * 64) void k_wgrad_lds(WgradArgs a, int til
   uint32_t a_off[A_I];
 #pragma unroll
   for (int i = 0; i < A_I; ++i) {
-    const int q = min(wave * A_I + i, A_T - 1);
-    const int sub = q / (BP / ARPI), row = (q % (BP / ARPI)) * ARPI + lane / ACPR;
-    const int n = n0 + sub * AW + ((lane % ACPR) ^ swz<AW>(row)) * 8;
+    const int row = min(wave * A_I + i, A_T - 1) * ARPI + lane / ACPR;
+    const int n = n0 + ((lane % ACPR) ^ swz<BM>(row)) * 8;
     a_off[i] = n < N ? (uint32_t)((((size_t)mbeg + row) * a.lddz + n) * 2) : ~0u;
   }
   // this lane's reduction chunk: filter position and channel, the same for all
@@ -156,10 +148,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_wgrad_lds(WgradArgs a, int til
   };
   int a_fo[TM], b_fo[TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int col = wm * WTM + i * 32;
-    a_fo[i] = (col / AW) * (BP * AW) + frag_off(col % AW, std::integral_constant<int, AW>{});
-  }
+  for (int i = 0; i < TM; ++i) a_fo[i] = frag_off(wm * WTM + i * 32, std::integral_constant<int, BM>{});
 #pragma unroll
   for (int j = 0; j < TN; ++j) b_fo[j] = frag_off(wn * WTN + j * 32, std::integral_constant<int, BN>{});
   auto frag = [&](const bf16_t* p, int pitch) __attribute__((always_inline)) {
@@ -177,7 +166,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_wgrad_lds(WgradArgs a, int til
     for (int p = 0; p < BP / 16; ++p) {
       bf16x8_t af[TM], bf[TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) af[i] = frag(sa + a_fo[i] + p * 16 * AW, AW);
+      for (int i = 0; i < TM; ++i) af[i] = frag(sa + a_fo[i] + p * 16 * BM, BM);
 #pragma unroll
       for (int j = 0; j < TN; ++j) bf[j] = frag(sb + b_fo[j] + p * 16 * BN, BN);
 #pragma unroll
@@ -189,17 +178,17 @@ __global__ __launch_bounds__(WM * WN * 64) void k_wgrad_lds(WgradArgs a, int til
   };
 
   if (nk > 0) {
-    static_for<0, NS - 1>([&](auto I) __attribute__((always_inline)) { copy(I); });
+    copy(std::integral_constant<int, 0>{});
     int k = 0;
     while (true) {
       bool done = false;
-      static_for<0, NS>([&](auto I) __attribute__((always_inline)) {
+      static_for<0, 2>([&](auto I) __attribute__((always_inline)) {
         constexpr int i = decltype(I)::value;
         if (!done) {
           // this wave's copies of step k have landed; past the barrier so have
           // the others', and all waves have read the buffer that is refilled
-          wait_step<(NS - 2) * LOADS>();
-          copy(std::integral_constant<int, (i + NS - 1) % NS>{});
+          wait_step<0>();
+          copy(std::integral_constant<int, 1 - i>{});
           __builtin_amdgcn_sched_barrier(0);
           multiply(I);
           done = ++k == nk;
@@ -239,18 +228,18 @@ __global__ __launch_bounds__(WM * WN * 64) void k_wgrad_lds(WgradArgs a, int til
     }
 }
 
-template <int BM, int BN, int WM, int WN, int BP, int NS, bool GRID>
+template <int BM, int BN, int WM, int WN, int BP, bool GRID>
 hipError_t go(const WgradArgs& a, hipStream_t s) {
   const int K = a.R * a.S * a.C;
   const int tn = (a.N + BM - 1) / BM, tk = (K + BN - 1) / BN;
   const double flops = 2.0 * a.nb * (a.Ho > 0 ? a.Ho * a.Wo : a.H * a.W) * (double)a.N * K;
   static const struct Name {
     char s[64];
-    Name() { snprintf(s, sizeof s, "k_wgrad_lds<%d,%d,%d,%d,%d,%d,%s>", BM, BN, WM, WN, BP, NS, GRID ? "true" : "false"); }
+    Name() { snprintf(s, sizeof s, "k_wgrad_lds<%d,%d,%d,%d,%d,%s>", BM, BN, WM, WN, BP, GRID ? "true" : "false"); }
   } name;
   WgradArgs b = a;
   b.direct = a.splits == 1;
-  XP_LAUNCH(name.s, flops, (k_wgrad_lds<BM, BN, WM, WN, BP, NS, GRID>), dim3(tn * tk * a.splits), dim3(WM * WN * 64), 0,
+  XP_LAUNCH(name.s, flops, (k_wgrad_lds<BM, BN, WM, WN, BP, GRID>), dim3(tn * tk * a.splits), dim3(WM * WN * 64), 0,
             s, b, tn, tk);
   return hipGetLastError();
 }
@@ -282,8 +271,8 @@ int wgrad_lds_splits(int M, int splits) {
 hipError_t launch_wgrad_lds(const WgradArgs& a, hipStream_t s) {
   const bool grid = a.Ho > 0 || a.pad != a.padw;
   if (tile_rows(a.N, (int64_t)a.nb * (a.Ho > 0 ? a.Ho * a.Wo : a.H * a.W)) == 128)
-    return grid ? go<128, 64, 4, 2, 64, 2, true>(a, s) : go<128, 64, 4, 2, 64, 2, false>(a, s);
-  return grid ? go<64, 64, 2, 2, 64, 2, true>(a, s) : go<64, 64, 2, 2, 64, 2, false>(a, s);
+    return grid ? go<128, 64, 4, 2, 64, true>(a, s) : go<128, 64, 4, 2, 64, false>(a, s);
+  return grid ? go<64, 64, 2, 2, 64, true>(a, s) : go<64, 64, 2, 2, 64, false>(a, s);
 }
 
 }  // namespace xp
