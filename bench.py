@@ -63,22 +63,18 @@ def source_hash():
 
 def kernel_key(name):
     """Common key for rocprofv3's demangled kernel names and the library's
-    launch names: no namespace or arguments, storage types as bf16 / f32, and
-    without the template arguments only the compiler's name shows (the GEMM's
-    gather mode, named by the library only when not 0; the weight gradient's
-    grid flag, named only when set; the row kernels' rows per trip; the
-    pools' channels per thread)."""
+    launch names: no namespaces or arguments, storage types as bf16 / f32, and
+    without the template arguments only the compiler's name shows (the general
+    GEMM's gather mode, named by the library only when not 0; the row kernels'
+    rows per trip; the pools' channels per thread)."""
     import re
-    n = name.split("(")[0].replace("void ", "").replace("xp::", "")
+    n = name.replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "").replace("xp::", "")
     n = n.replace("unsigned short", "bf16").replace(" ", "")
     n = n.replace("<float", "<f32").replace(",float", ",f32")
     m = re.match(r"^k_conv_gemm<((?:[^,>]+,){7}[^,>]+),(\d)>$", n)
     if m:
         gm = int(m.group(2))
         n = "k_conv_gemm<" + m.group(1) + ("" if gm == 0 else "," + ("strided", "strided_dgrad")[gm - 1]) + ">"
-    m = re.match(r"^k_wgrad_t<((?:\d+,){4}\d+),(true|false)>$", n)
-    if m:
-        n = "k_wgrad_t<" + m.group(1) + (",grid>" if m.group(2) == "true" else ">")
     return re.sub(r"^(k_bn_apply_v|k_bn_bwd_v|k_maxpool3s2_fwd|k_maxpool3s2_bwd)<(bf16|f32),\d+>$",
                   r"\1<\2>", n)
 
@@ -533,11 +529,11 @@ def vendor_reference(off_us, reps=50):
     """The stage's convolution shapes (32 x 35 x 35 NHWC, bf16) against the
     vendor libraries, per launch, with HIP events over back-to-back launches.
     Forward: this library's implicit GEMM (forward of a one-convolution
-    stage: one k_conv_gemm launch), MIOpen's convolution through torch
+    stage: one k_conv_gemm_lds launch), MIOpen's convolution through torch
     (channels-last), and hipBLASLt's plain GEMM of the same M x K x N through
     torch.mm (no im2col: the library GEMM reads a ready K-major operand, which
     the convolution does not have).  Weight gradient: this library's
-    k_wgrad_t plus its split reduction (per-launch events in the one-
+    k_wgrad_lds plus its split reduction (per-launch events in the one-
     convolution stage's backward, event offset removed) against MIOpen's
     backward-weights convolution.  Context for the MFMA fraction of these
     skinny shapes, not a dependency: the stage itself never calls the vendor

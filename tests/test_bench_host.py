@@ -43,6 +43,38 @@ def test_every_called_module_name_is_defined():
     assert not missing, sorted(missing)
 
 
+KERNEL_NAMES = [
+    # the compiler's name, as a profiler prints it; the library's launch name
+    ("void xp::(anonymous namespace)::k_conv_gemm_lds<96, 96, 1, 3, 32, 3, false, 0, false, false>(xp::ConvArgs, int)",
+     "k_conv_gemm_lds<96,96,1,3,32,3,false,0,false,false>"),
+    ("void xp::(anonymous namespace)::k_conv_gemm_lds<32, 32, 1, 1, 64, 4, true, 0, false, true>(xp::ConvArgs, int)",
+     "k_conv_gemm_lds<32,32,1,1,64,4,true,0,false,true>"),
+    ("void xp::(anonymous namespace)::k_conv_gemm_lds<64, 64, 2, 2, 64, 2, true, 2, true, false>(xp::ConvArgs, int)",
+     "k_conv_gemm_lds<64,64,2,2,64,2,true,2,true,false>"),
+    ("void xp::(anonymous namespace)::k_wgrad_lds<128, 64, 4, 2, 64, false>(xp::WgradArgs, int, int)",
+     "k_wgrad_lds<128,64,4,2,64,false>"),
+    ("void xp::(anonymous namespace)::k_wgrad_lds<64, 64, 2, 2, 64, true>(xp::WgradArgs, int, int)",
+     "k_wgrad_lds<64,64,2,2,64,true>"),
+    ("void xp::(anonymous namespace)::k_conv_gemm_image<7>(xp::ConvArgs, int, int, int, int)", "k_conv_gemm_image<7>"),
+    ("void xp::(anonymous namespace)::k_wgrad_image<5>(xp::WgradArgs, int, int, int, int)", "k_wgrad_image<5>"),
+    ("void xp::k_conv_gemm<unsigned short, 32, 64, 2, 2, false, 4, 2, 0>(xp::ConvArgs)",
+     "k_conv_gemm<bf16,32,64,2,2,false,4,2>"),
+    ("void xp::k_conv_gemm<float, 64, 64, 2, 2, false, 1, 1, 2>(xp::ConvArgs)",
+     "k_conv_gemm<f32,64,64,2,2,false,1,1,strided_dgrad>"),
+    ("void xp::k_wgrad<float, 64, 64, 2, 2, false>(xp::WgradArgs)", "k_wgrad<f32,64,64,2,2,false>"),
+    ("xp::k_colfinal_v(xp::ColArgs)", "k_colfinal_v"),
+]
+
+
+def test_profiler_and_launch_names_of_a_kernel_share_a_key():
+    """Stored HBM traffic is looked up by launch name and stored by the profiler's."""
+    sys.path.insert(0, ROOT)
+    import bench
+    keys = [bench.kernel_key(a) for a, _ in KERNEL_NAMES]
+    assert keys == [bench.kernel_key(b) for _, b in KERNEL_NAMES]
+    assert all(k.startswith("k_") for k in keys) and len(set(keys)) == len(keys)
+
+
 def test_multi_gpu_request_exits_with_a_message():
     r = subprocess.run([sys.executable, BENCH, "--gpus", "2"], capture_output=True, text=True,
                        cwd=ROOT, timeout=120)
