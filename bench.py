@@ -8,7 +8,8 @@ tensors already resident in HBM.
 
 Prints ONE JSON line: stage samples/s (value), the predict / Adam HBM rates
 of the 1e8-parameter sweep, the roofline of the dominant kernel, and the CPU
-oracle timed on a bounded sample.
+oracle timed on a bounded sample.  The line is a few kilobytes; every figure
+measured goes to stderr.
 
 usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME] [--dtype bf16|f32]
 """
@@ -777,6 +778,39 @@ def config_legs(args, off_us):
     return out
 
 
+def result_line(out):
+    """The result line: every figure of `out` at a length that a log's last few
+    kilobytes hold (the whole of it goes to stderr as a line of its own)."""
+    def pick(d, *keys):
+        return {k: d[k] for k in keys if k in d}
+
+    line = dict(out)
+    line["top_kernels"] = [[k["kernel"], k["ms_per_step"], k["launches_per_step"], k["frac"]]
+                           for k in out["top_kernels"][:5]]
+    for k in ("roofline_conv_gemm", "roofline_weight_gradient"):
+        if out.get(k):
+            line[k] = pick(out[k], "kernel", "achieved", "unit", "frac", "avg_launch_us")
+    if "peaks_measured" in out:
+        line["peaks_measured"] = pick(out["peaks_measured"], "hbm_copy_GB_s", "mfma_bf16_TFLOP_s")
+    if "predict_adam_sweep" in out:
+        sw = out["predict_adam_sweep"]
+        line["predict_adam_sweep"] = {"n_params": sw["n_params"],
+                                      "GB_s": {k: v["GB_s"] for k, v in sw.items() if isinstance(v, dict) and "GB_s" in v}}
+    if "interleaved_schedule" in out:
+        line["interleaved_schedule"] = pick(out["interleaved_schedule"], "samples_per_s", "ms_per_minibatch")
+    for k in ("vgg16_partitioned", "resnet101_partitioned", "inception_v3_partitioned"):
+        if k in out:
+            line[k] = {"ms_per_stage": [st["ms_per_step"] for st in out[k]["per_stage"]]}
+    if "vendor_reference" in out:
+        line["vendor_reference"] = [[v["shape"].split(",")[0]] + [v[k] for k in v if k.endswith("_us") and k != "event_offset_us"]
+                                    for v in out["vendor_reference"]]
+    if "configs" in out:
+        line["configs"] = [pick(c, "workload", "dtype", "s_fwd", "ms_per_step", "mfma_util_all_gemm") for c in out["configs"]]
+    if "cpu_baseline" in out:
+        line["cpu_baseline"] = pick(out["cpu_baseline"], "value", "unit", "cores", "kind", "sample")
+    return line
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -867,7 +901,8 @@ def main():
         out["configs"] = config_legs(args, off_us)
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(w, args.dtype)
-    print(json.dumps(out))
+    print("all figures: " + json.dumps(out), file=sys.stderr)
+    print(json.dumps(result_line(out)))
 
 
 if __name__ == "__main__":
