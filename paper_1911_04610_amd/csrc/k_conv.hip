@@ -625,8 +625,9 @@ hipError_t pick_step(const ConvArgs& a, int64_t rows, hipStream_t s, int* row_ti
 template <int GM, bool DG>
 hipError_t few(const ConvArgs& a, hipStream_t s, int* row_tiles) {
   if (a.C % 64 != 0) return go<32, 32, 1, 1, 64, 4, true, GM, DG, true>(a, s, row_tiles);
-  if ((int64_t)a.R * a.S * a.C >= 4096) return go<32, 32, 1, 1, 64, 8, false, GM, DG, true>(a, s, row_tiles);
-  return go<32, 32, 1, 1, 64, 4, false, GM, DG, true>(a, s, row_tiles);
+  if (DG || (int64_t)a.R * a.S * a.C >= 4096)  // (a data gradient comes here from 4096 on)
+    return go<32, 32, 1, 1, 64, 8, false, GM, DG, true>(a, s, row_tiles);
+  if constexpr (!DG) return go<32, 32, 1, 1, 64, 4, false, GM, DG, true>(a, s, row_tiles);
 }
 
 }  // namespace

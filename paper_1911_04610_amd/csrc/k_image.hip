@@ -15,6 +15,7 @@
 #include "xp_kernels.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
 
 namespace xp {
@@ -434,8 +435,17 @@ hipError_t conv_go(const ConvArgs& a, int groups, int rb, const Rows& l, int row
   } name;
   const double rows = a.Ho > 0 ? (double)a.Ho * a.Wo : (double)a.H * a.W;
   const auto kernel = k_conv_gemm_image<R>;
-  const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, CONV_LDS);
+  // the LDS above the default limit, allowed once per device (two threads may both ask)
+  static std::atomic<uint64_t> allowed{0};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+  if (!(allowed.load(std::memory_order_acquire) & bit)) {
+    e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, CONV_LDS);
+    if (e != hipSuccess) return e;
+    allowed.fetch_or(bit, std::memory_order_release);
+  }
   XP_LAUNCH(name.s, 2.0 * a.nb * rows * a.N * a.R * a.S * a.C, kernel, dim3(groups, (a.N + 63) / 64), dim3(256), lds,
             s, a, rb, l.lead, l.pitch, row_blocks);
   return hipGetLastError();
