@@ -1,8 +1,10 @@
-"""The tiles and gathers of the bf16 convolution that copies its operands
-straight into LDS (csrc/k_conv.hip, k_wgrad.hip), each through a small stage whose sizes
-reach it with a ragged last tile, against the oracle's bf16 model (and the exact
-one where no ReLU is present) at the bf16 bar, 2e-2; and the fp32 tiles of
-csrc/k_gemm.hip against the exact oracle.
+"""The tiles and gathers of the bf16 convolutions that copy their operands straight
+into LDS (csrc/k_conv.hip, k_wgrad.hip) and of the image kernels (k_image.hip), and
+which calls each of them takes, each through a small stage whose sizes reach it with
+a ragged last tile: every tile of k_conv_gemm_lds by its launch name against 64-bit
+autograd, and cases against the oracle's bf16 model (and the exact one where no ReLU
+is present) at the bf16 bar, 2e-2, with the launches that they are there for; and
+the fp32 tiles of csrc/k_gemm.hip against the exact oracle.
 
 A case is picked by rows (micro-batch x H x W), output channels and input
 channels: channels that are no multiple of the 64-channel step take a filter
@@ -35,7 +37,7 @@ CASES = {
     "128x64_bias_relu": ([conv(-1, 48, 64, 3, True), relu(0)], (129, 128, 48), 4),
     "96x96": ([conv(-1, 32, 96, 3), bn(0, 96)], (91, 91, 32), 4),
     "96x96_chunk_taps": ([conv(-1, 24, 88, 5)], (91, 91, 24), 4),
-    "128x32": ([conv(-1, 64, 24, 3, True)], (57, 57, 64), 4),
+    "few_tiles_24_channels": ([conv(-1, 64, 24, 3, True)], (57, 57, 64), 4),
     "strided": ([conv(-1, 64, 256, 3, stride=2)], (57, 55, 64), 4),
     "strided_1x1": ([conv(-1, 256, 512, 1, stride=2)], (81, 80, 256), 4),
     "strided_7x7_chunk_taps": ([conv(-1, 40, 256, 7, stride=2)], (57, 56, 40), 4),
@@ -45,7 +47,7 @@ CASES = {
     "few_tiles_long": ([conv(-1, 512, 48, 3, True), relu(0)], (7, 7, 512), 3),
     "few_tiles_chunk_taps": ([conv(-1, 24, 40, 7), bn(0, 40)], (9, 11, 24), 3),
     "few_tiles_one_step": ([conv(-1, 40, 8, 1)], (9, 11, 40), 3),
-    "few_tiles_bn_partials": ([conv(-1, 64, 128, 1), bn(0, 128), relu(1), conv(2, 128, 64, 5)], (9, 10, 64), 3),
+    "general_bn_partials": ([conv(-1, 64, 128, 1), bn(0, 128), relu(1), conv(2, 128, 64, 5)], (9, 10, 64), 3),
     "few_tiles_strided": ([conv(-1, 64, 64, 3, stride=2)], (23, 25, 64), 2),
     # output channels that are no multiple of 8: the general kernel's large tiles
     "general_128x128": ([conv(-1, 32, 132, 1)], (129, 128, 32), 4),
@@ -83,9 +85,66 @@ CASES = {
 }
 
 
+# launches that a case is there for
+REACHES = {
+    "64x64": ["k_conv_gemm_lds<64,64,2,2,64,2,false,0,false,false>", "k_wgrad_lds<128,64,4,2,64,false>"],
+    "64x64_chunk_taps": ["k_conv_gemm_lds<64,64,2,2,64,2,true,0,false,false>", "k_wgrad_lds<128,64,4,2,64,false>"],
+    "64x64_8_channels_1x7": ["k_conv_gemm_lds<64,64,2,2,64,2,true,0,false,false>", "k_wgrad_lds<128,64,4,2,64,true>"],
+    "64x128": ["k_conv_gemm_lds<64,128,2,2,64,2,false,0,false,false>", "k_wgrad_lds<128,64,4,2,64,false>"],
+    "128x128_chunk_taps": ["k_conv_gemm_lds<128,128,4,2,64,2,true,0,false,false>",
+                           "k_wgrad_lds<128,64,4,2,64,false>"],
+    "128x64_bias_relu": ["k_conv_gemm_lds<128,64,4,2,64,2,true,0,false,false>", "k_wgrad_lds<64,64,2,2,64,false>"],
+    "96x96": ["k_conv_gemm_lds<96,96,1,3,32,3,false,0,false,false>", "k_wgrad_lds<128,64,4,2,64,false>"],
+    "96x96_chunk_taps": ["k_conv_gemm_lds<96,96,1,3,32,3,true,0,false,false>", "k_wgrad_lds<128,64,4,2,64,false>"],
+    "few_tiles_24_channels": ["k_conv_gemm_lds<32,32,1,1,64,4,false,0,false,true>",
+                              "k_wgrad_lds<64,64,2,2,64,false>"],
+    "strided": ["k_conv_gemm_lds<64,64,2,2,64,2,false,1,false,false>", "k_wgrad_lds<128,64,4,2,64,true>"],
+    "strided_1x1": ["k_conv_gemm_lds<64,128,2,2,64,2,false,1,false,false>", "k_wgrad_lds<128,64,4,2,64,true>"],
+    "strided_7x7_chunk_taps": ["k_conv_gemm_lds<64,64,2,2,64,2,true,1,false,false>",
+                               "k_wgrad_lds<128,64,4,2,64,true>"],
+    "unpadded": ["k_conv_gemm_lds<64,64,2,2,64,2,false,1,false,false>", "k_wgrad_lds<128,64,4,2,64,true>"],
+    "few_tiles": ["k_conv_gemm_lds<32,32,1,1,64,4,false,0,false,true>", "k_wgrad_lds<64,64,2,2,64,false>"],
+    "few_tiles_long": ["k_conv_gemm_lds<32,32,1,1,64,8,false,0,false,true>", "k_wgrad_lds<64,64,2,2,64,false>"],
+    "few_tiles_chunk_taps": ["k_conv_gemm_lds<32,32,1,1,64,4,true,0,false,true>", "k_wgrad_lds<64,64,2,2,64,false>"],
+    "few_tiles_one_step": ["k_conv_gemm_lds<32,32,1,1,64,4,true,0,false,true>", "k_wgrad_lds<64,64,2,2,64,false>"],
+    "general_bn_partials": ["k_conv_gemm<bf16,64,64,2,2,false,4,2>"],
+    "few_tiles_strided": ["k_conv_gemm_lds<32,32,1,1,64,4,false,1,false,true>", "k_wgrad_lds<64,64,2,2,64,true>"],
+    "general_128x128": ["k_conv_gemm<bf16,128,128,2,4,false,2,2>", "k_wgrad<bf16,128,64,2,2,false>"],
+    "general_128x64": ["k_conv_gemm<bf16,128,64,2,2,false,2,2>", "k_wgrad<bf16,64,128,2,2,false>"],
+    "general_64x96": ["k_conv_gemm<bf16,64,96,2,2,false,1,2>", "k_wgrad<bf16,128,128,2,2,false>"],
+    "general_odd_channels": ["k_conv_gemm<bf16,64,96,2,2,false,1,2>", "k_wgrad<bf16,128,128,2,2,false>"],
+    "general_odd_channels_1x1": ["k_conv_gemm<bf16,32,64,2,2,false,2,2>", "k_wgrad<bf16,128,128,2,2,false>"],
+    "general_64x64_1x1": ["k_conv_gemm<bf16,64,64,2,2,false,2,2>", "k_wgrad<bf16,128,64,2,2,false>"],
+    "general_64x64_5x5": ["k_conv_gemm<bf16,64,64,2,2,false,8,2>", "k_wgrad<bf16,128,128,2,2,false>"],
+    "general_strided_128x128": ["k_conv_gemm<bf16,128,128,2,4,false,2,2,strided>", "k_wgrad<bf16,128,64,2,2,false>"],
+    "general_strided_128x64": ["k_conv_gemm<bf16,128,64,2,2,false,2,2,strided>", "k_wgrad<bf16,64,64,2,2,false>"],
+    "general_strided_64x96": ["k_conv_gemm<bf16,64,96,2,2,false,1,2,strided>", "k_wgrad<bf16,128,64,2,2,false>"],
+    "image_7x7_s2": ["k_conv_gemm_image<7>", "k_wgrad_image<5>"],
+    "image_7x7_s2_channels_72": ["k_conv_gemm_image<7>", "k_wgrad_image<5>"],
+    "image_3x3": ["k_conv_gemm_image<3>", "k_wgrad_image<1>"],
+    "image_3x3_odd": ["k_conv_gemm_image<3>", "k_wgrad_image<1>"],
+    "image_3x3_small": ["k_conv_gemm<bf16,64,32,2,2,true,1,2>", "k_wgrad<bf16,64,64,2,2,true>"],
+    "image_3x3_s2_unpadded": ["k_conv_gemm_image<3>", "k_wgrad_image<1>"],
+    "image_5x5": ["k_conv_gemm_image<5>", "k_wgrad_image<3>"],
+    "image_least_map": ["k_conv_gemm_image<5>", "k_wgrad_image<3>"],
+    "image_least_map_s2": ["k_conv_gemm_image<7>", "k_wgrad_image<5>"],
+    "image_least_wgrad_map": ["k_conv_gemm<bf16,64,64,2,2,true,2,2>", "k_wgrad<bf16,128,128,2,2,true>"],
+    "image_wgrad_150_channels": ["k_conv_gemm<bf16,64,64,2,2,true,2,2>", "k_wgrad_image<5>"],
+    "image_wgrad_44_channels_s2": ["k_conv_gemm<bf16,64,32,2,2,true,1,2,strided>", "k_wgrad_image<3>"],
+    "odd_linear": ["k_conv_gemm<bf16,64,64,2,2,true,2,2>", "k_wgrad<bf16,128,128,2,2,true>"],
+    "image_one_channel": ["k_conv_gemm<bf16,64,32,2,2,true,1,2>", "k_wgrad_image<1>"],
+    "bn_partials": ["k_conv_gemm_lds<128,128,4,2,64,2,false,0,true,false>"],
+    "bn_partials_96": ["k_conv_gemm_lds<96,96,1,3,32,3,false,0,false,false>",
+                       "k_conv_gemm<bf16,64,96,2,2,false,1,2>"],
+    "bn_partials_strided": ["k_conv_gemm_lds<64,128,2,2,64,2,false,2,true,false>"],
+}
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_conv_tiles_match_oracle(name):
     layers, shape, mb = CASES[name]
+    launched = sum(_launches(xp.Stage(layers, mb, 1, shape, xp.BF16), shape, mb), [])
+    assert set(REACHES[name]) <= set(launched), launched
     w = wl.StageWorkload(name, layers, mb, 1, shape, 1, 0, 0, 0, minibatches=1, seed=131)
     inp = wl.stage_inputs(w, act_dtype="bf16")
     gpu, _ = run_stage(w, inp, xp.BF16, xp.Hyper(), 0, 0, minibatches=1)
@@ -221,6 +280,202 @@ def _launches(st, shape, mb, dtype=xp.BF16):
     return out
 
 
+# One call for each tile, step (whole 64 channels, or a filter tap per 16-byte chunk),
+# grid and direction of k_conv_gemm_lds, by its launch name's arguments:
+# (filter, input channels, output channels, rows, columns, micro-batch, stride)
+LDS_CASES = {
+    "128,32,4,1,64,2,false,0,false,false": (3, 64, 32, 79, 78, 4, 1),
+    "128,32,4,1,64,2,true,0,false,false": (3, 40, 24, 79, 78, 4, 1),
+    "64,64,2,2,64,2,false,0,false,false": (1, 64, 200, 57, 55, 2, 1),
+    "64,64,2,2,64,2,true,0,false,false": (1, 72, 200, 57, 55, 2, 1),
+    "64,128,2,2,64,2,false,0,false,false": (1, 64, 256, 57, 57, 4, 1),
+    "64,128,2,2,64,2,true,0,false,false": (1, 72, 256, 57, 57, 4, 1),
+    "128,128,4,2,64,2,false,0,false,false": (1, 64, 512, 57, 57, 4, 1),
+    "128,128,4,2,64,2,true,0,false,false": (1, 40, 512, 57, 57, 4, 1),
+    "96,96,1,3,32,3,false,0,false,false": (1, 32, 96, 91, 91, 4, 1),
+    "96,96,1,3,32,3,true,0,false,false": (1, 40, 88, 91, 91, 4, 1),
+    "128,64,4,2,64,2,false,0,false,false": (1, 64, 64, 129, 128, 4, 1),
+    "128,64,4,2,64,2,true,0,false,false": (1, 72, 64, 129, 128, 4, 1),
+    "32,32,1,1,64,4,false,0,false,true": (3, 64, 40, 7, 9, 3, 1),
+    "32,32,1,1,64,4,true,0,false,true": (5, 24, 40, 7, 9, 3, 1),
+    "32,32,1,1,64,8,false,0,false,true": (3, 512, 40, 7, 9, 3, 1),
+    "128,32,4,1,64,2,false,1,false,false": (3, 64, 32, 113, 111, 4, 2),
+    "128,32,4,1,64,2,true,1,false,false": (3, 40, 24, 113, 111, 4, 2),
+    "64,64,2,2,64,2,false,1,false,false": (1, 64, 256, 57, 55, 4, 2),
+    "64,64,2,2,64,2,true,1,false,false": (1, 72, 256, 57, 55, 4, 2),
+    "64,128,2,2,64,2,false,1,false,false": (1, 64, 512, 81, 80, 4, 2),
+    "64,128,2,2,64,2,true,1,false,false": (1, 72, 512, 81, 80, 4, 2),
+    "128,128,4,2,64,2,false,1,false,false": (1, 64, 512, 113, 112, 4, 2),
+    "128,128,4,2,64,2,true,1,false,false": (1, 72, 512, 113, 112, 4, 2),
+    "96,96,1,3,32,3,false,1,false,false": (1, 64, 96, 182, 181, 4, 2),
+    "96,96,1,3,32,3,true,1,false,false": (1, 40, 88, 182, 181, 4, 2),
+    "128,64,4,2,64,2,false,1,false,false": (1, 64, 64, 257, 255, 4, 2),
+    "128,64,4,2,64,2,true,1,false,false": (1, 72, 64, 257, 255, 4, 2),
+    "32,32,1,1,64,4,false,1,false,true": (3, 64, 40, 13, 15, 3, 2),
+    "32,32,1,1,64,4,true,1,false,true": (5, 24, 40, 13, 15, 3, 2),
+    "32,32,1,1,64,8,false,1,false,true": (3, 512, 40, 13, 15, 3, 2),
+    "64,64,2,2,64,2,false,0,true,false": (3, 64, 256, 65, 64, 4, 1),
+    "64,64,2,2,64,2,true,0,true,false": (3, 64, 232, 65, 64, 4, 1),
+    "64,128,2,2,64,2,false,0,true,false": (1, 128, 1024, 57, 55, 4, 1),
+    "64,128,2,2,64,2,true,0,true,false": (1, 128, 1032, 57, 55, 4, 1),
+    "128,128,4,2,64,2,false,0,true,false": (1, 128, 64, 79, 79, 4, 1),
+    "128,128,4,2,64,2,true,0,true,false": (1, 128, 136, 79, 79, 4, 1),
+    "96,96,1,3,32,3,false,0,true,false": (1, 96, 256, 91, 91, 2, 1),
+    "96,96,1,3,32,3,true,0,true,false": (1, 88, 264, 91, 91, 2, 1),
+    "128,64,4,2,64,2,false,0,true,false": (1, 64, 64, 91, 91, 4, 1),
+    "128,64,4,2,64,2,true,0,true,false": (1, 56, 136, 91, 91, 4, 1),
+    "32,32,1,1,64,4,true,0,true,true": (3, 64, 488, 7, 9, 3, 1),
+    "32,32,1,1,64,8,false,0,true,true": (3, 64, 512, 7, 9, 3, 1),
+    "128,32,4,1,64,2,false,2,true,false": (3, 32, 128, 19, 17, 3, 2),
+    "128,32,4,1,64,2,true,2,true,false": (3, 24, 120, 19, 17, 3, 2),
+    "64,64,2,2,64,2,false,2,true,false": (3, 64, 64, 19, 17, 3, 2),
+    "64,64,2,2,64,2,true,2,true,false": (3, 72, 40, 19, 17, 3, 2),
+    "64,128,2,2,64,2,false,2,true,false": (1, 128, 320, 57, 55, 4, 2),
+    "64,128,2,2,64,2,true,2,true,false": (1, 128, 264, 57, 55, 4, 2),
+    "128,128,4,2,64,2,false,2,true,false": (1, 128, 64, 79, 79, 4, 2),
+    "128,128,4,2,64,2,true,2,true,false": (1, 128, 72, 79, 79, 4, 2),
+    "96,96,1,3,32,3,false,2,true,false": (1, 96, 288, 91, 91, 2, 2),
+    "96,96,1,3,32,3,true,2,true,false": (1, 88, 264, 91, 91, 2, 2),
+    "128,64,4,2,64,2,false,2,true,false": (1, 64, 320, 91, 91, 4, 2),
+    "128,64,4,2,64,2,true,2,true,false": (1, 56, 264, 91, 91, 4, 2),
+}
+
+
+def _conv64(x, w, stride):
+    """[n, h, w, c] by [n, r, s, c], same padding: one product per filter tap."""
+    import torch
+    k, (h, wd) = w.shape[1], x.shape[1:3]
+    x = torch.nn.functional.pad(x, (0, 0, k // 2, k // 2, k // 2, k // 2))
+    y = 0
+    for r in range(k):
+        for q in range(k):
+            t = x[:, r:r + h:stride, q:q + wd:stride]
+            y = y + t.reshape(-1, t.shape[3]) @ w[:, r, q].t()
+    return y.reshape(x.shape[0], (h - 1) // stride + 1, (wd - 1) // stride + 1, -1)
+
+
+def _bn_relu_conv_case(convs, x_shape, seed, expect):
+    """A batch norm, a ReLU and convolutions (k, cout, stride) of it whose outputs are
+    concatenated, forward and backward against 64-bit autograd.  Every tensor between
+    the layers is rounded to bf16 (2^-9 of a value at most, 1.1e-3 rms, three of them in a
+    row for dx and the batch norm's gradients) and a flipped ReLU mask is as rare as an
+    output within that of zero: 1e-2 of each result's norm."""
+    import torch
+    mb, h, w, cin = x_shape
+    layers = [bn(-1, cin), relu(0)] + [conv(1, cin, co, k, stride=s) for k, co, s in convs]
+    if len(convs) > 1:
+        layers.append(dict(kind="concat", inputs=list(range(2, 2 + len(convs)))))
+    st = xp.Stage(layers, mb, 1, (h, w, cin), xp.BF16)
+    fwd, bwd = _launches(st, (h, w, cin), mb)
+    assert expect in (fwd if expect.split(",")[8] == "false" else bwd), (expect, fwd, bwd)
+    st.grad.zero_()
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    params = [1 + torch.rand(cin, generator=g, device="cuda"), torch.randn(cin, generator=g, device="cuda")]
+    params += [(torch.randn(co, k, k, cin, generator=g, device="cuda") / (k * k * cin) ** 0.5).to(torch.bfloat16).float()
+               for k, co, s in convs]
+    for (off, cnt), t in zip(st.layout, params):
+        st.W[off:off + cnt] = t.reshape(-1)
+    for d in (xp.FWD, xp.BWD):
+        st.xpipe_predict_weights(d, 0, xp.Hyper(), 0)
+    x = torch.randn(x_shape, generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randn(st.out_shape, generator=g, device="cuda").to(torch.bfloat16)
+    y, dx = torch.empty_like(dy), torch.empty_like(x)
+    st.xpipe_stage_fwd(x, y)
+    st.xpipe_stage_bwd(x, dy, None, dx)
+    X = x.double().requires_grad_(True)
+    P = [t.double().requires_grad_(True) for t in params]
+    var, mean = torch.var_mean(X, (0, 1, 2), unbiased=False)
+    A = ((X - mean) * (var + 1e-5).rsqrt() * P[0] + P[1]).relu()
+    Y = torch.cat([_conv64(A, wt, s) for wt, (k, co, s) in zip(P[2:], convs)], 3)
+    Y.backward(dy.double())
+    pairs = {"y": (y, Y.detach()), "dx": (dx, X.grad)}
+    pairs.update({f"grad[{i}]": (st.grad[off:off + cnt], p.grad.reshape(-1))
+                  for i, ((off, cnt), p) in enumerate(zip(st.layout, P))})
+    e = {k: float((a.double() - b).norm() / b.norm()) for k, (a, b) in pairs.items()}
+    assert all(v <= 1e-2 for v in e.values()), e
+
+
+@pytest.mark.parametrize("args", list(LDS_CASES))
+def test_lds_copy_tiles(args):
+    k, cin, cout, h, w, mb, stride = LDS_CASES[args]
+    _bn_relu_conv_case([(k, cout, stride)], (mb, h, w, cin), 7, f"k_conv_gemm_lds<{args}>")
+
+
+@pytest.mark.parametrize("cout,chunks", [(64, "false"), (136, "true")])
+def test_lds_copy_widest_tile_accumulates(cout, chunks):
+    """256 x 256 tiles: the second of two data gradients adds to the first's and takes the
+    batch norm's partials (with the first's tile also its own stores)."""
+    _bn_relu_conv_case([(1, cout, 1), (3, cout, 1)], (5, 214, 245, 256), 9,
+                       f"k_conv_gemm_lds<256,256,2,4,64,2,{chunks},0,true,false>")
+
+
+@pytest.mark.parametrize("k,cin,cout,h,w,mb,stride,fwd,wgrad", [
+    (7, 3, 64, 25, 43, 2, 2, "k_conv_gemm_image<7>", "k_wgrad_image<5>"),
+    (3, 3, 72, 17, 19, 3, 1, "k_conv_gemm_image<3>", "k_wgrad_image<1>"),
+    (3, 9, 24, 11, 13, 3, 1, "k_conv_gemm<", "k_wgrad_image<3>"),
+    (1, 20, 16, 23, 19, 3, 2, "k_conv_gemm<", "k_wgrad_image<1>"),
+    (3, 64, 200, 57, 55, 2, 1, "k_conv_gemm_lds<64,64,", "k_wgrad_lds<128,64,"),
+    (5, 24, 200, 57, 55, 2, 1, "k_conv_gemm_lds<64,64,", "k_wgrad_lds<128,64,"),
+    (3, 64, 40, 7, 9, 3, 1, "k_conv_gemm_lds<32,32,", "k_wgrad_lds<64,64,"),
+    (5, 24, 40, 13, 15, 3, 2, "k_conv_gemm_lds<32,32,", "k_wgrad_lds<64,64,"),
+    (1, 128, 136, 57, 55, 4, 2, "k_conv_gemm_lds<64,64,", "k_wgrad_lds<128,64,"),
+    (3, 64, 73, 7, 9, 3, 1, "k_conv_gemm<", "k_wgrad<")])
+def test_values_that_are_not_finite_stay_in_their_sums(k, cin, cout, h, w, mb, stride, fwd, wgrad):
+    """An infinity in the input and a NaN in the output gradient reach the results whose
+    sums they are in, and no other changes a bit: what the kernels read past a row, a
+    reduction or the last pixel is zero on both sides."""
+    import torch
+    st = xp.Stage([conv(-1, cin, cout, k, stride=stride)], mb, 1, (h, w, cin), xp.BF16)
+    names = _launches(st, (h, w, cin), mb)
+    assert any(n.startswith(fwd) for n in names[0]) and any(n.startswith(wgrad) for n in names[1]), names
+    g = torch.Generator(device="cuda").manual_seed(3)
+    st.W.normal_(generator=g)
+    for d in (xp.FWD, xp.BWD):
+        st.xpipe_predict_weights(d, 0, xp.Hyper(), 0)
+    x = torch.randn(mb, h, w, cin, generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randn(st.out_shape, generator=g, device="cuda").to(torch.bfloat16)
+
+    def run(x, dy):
+        y, dx = torch.empty_like(dy), torch.empty_like(x)
+        st.grad.zero_()
+        st.xpipe_stage_fwd(x, y)
+        st.xpipe_stage_bwd(x, dy, None, dx)
+        return y, dx, st.grad[:cout * k * k * cin].reshape(cout, k, k, cin).clone()
+
+    def check(got, clean, touched):
+        assert not bool(torch.isfinite(got[touched]).any())
+        assert bool(torch.equal(got[~touched], clean[~touched]))
+
+    ones = torch.ones(1, k, k, 1, device="cuda", dtype=torch.double)
+    clean = run(x, dy)
+    assert all(bool(torch.isfinite(t).all()) for t in clean)
+    for at in ((mb - 1, h - 1, w - 1), (0, h // 2, w - 1), (0, 0, 0)):
+        bad = x.clone()
+        bad[at][cin - 1] = float("inf")
+        here = torch.zeros(mb, h, w, 1, device="cuda", dtype=torch.double)
+        here[at] = 1
+        y, _, gw = run(bad, dy)
+        check(y, clean[0], (_conv64(here, ones, stride) > 0).expand_as(y))
+        taps = torch.zeros(cout, k, k, cin, dtype=torch.bool, device="cuda")
+        for r in range(k):
+            for q in range(k):
+                one = torch.zeros_like(ones)
+                one[0, r, q] = 1
+                taps[:, r, q, cin - 1] = bool((_conv64(here, one, stride) > 0).any())
+        check(gw, clean[2], taps)
+    n, ho, wo, _ = st.out_shape
+    at = (n - 1, ho // 2, wo // 2)
+    bad = dy.clone()
+    bad[at][cout - 1] = float("nan")
+    _, dx, gw = run(x, bad)
+    here = torch.zeros(mb, h, w, 1, device="cuda", dtype=torch.double, requires_grad=True)
+    _conv64(here, ones, stride)[at].sum().backward()
+    check(dx, clean[1], (here.grad > 0).expand_as(dx))
+    rows = torch.zeros(cout, k, k, cin, dtype=torch.bool, device="cuda")
+    rows[cout - 1] = True
+    check(gw, clean[2], rows)
+
+
 LINEAR = dict(kind="linear", inputs=[-1], cin=100, cout=200, bias=False)
 
 
@@ -272,7 +527,8 @@ def test_lds_copy_kernel_takes_what_it_does_faster(k, cin, cout, hw, mb, stride,
 
 
 @pytest.mark.parametrize("cin,rows64,tile", [
-    (16, 200, "32,32"), (16, 300, "32,32"), (16, 469, "64,32"), (32, 469, "64,32"), (64, 469, "32,32"), (16, 600, "32,32"), (16, 700, "64,32"),
+    (16, 200, "32,32"), (16, 300, "32,32"), (16, 469, "64,32"), (32, 469, "64,32"), (64, 469, "32,32"),
+    (16, 600, "32,32"), (16, 700, "64,32"),
     (10, 120, "32,32"), (10, 200, "64,32"), (10, 300, "64,32")])
 def test_f32_narrow_tiles(cin, rows64, tile):
     """Up to 32 columns in fp32 storage: 32-row tiles where they shorten the last round."""
@@ -349,14 +605,15 @@ def test_bn_partials_of_near_constant_channels():
     assert float(((st.grad[bo:bo + bc].double() - ref) / ref).abs().max()) <= 2.0 ** -23
 
 
-def test_wide_data_gradient_tile():
+@pytest.mark.parametrize("cout", [64, 136])
+def test_wide_data_gradient_tile(cout):
     """256 x 256 tiles (rows of 256 columns in one workgroup): the masked data
     gradient of a 1 x 1 convolution over 262 160 rows, against fp64 products.
     Bound per value: half a unit in bf16's last place (8 significant bits: 2^-8 of
-    the value) of a sum that 16 fp32 additions left within 16 x 2^-24 of the sum
+    the value) of a sum that `cout` fp32 additions left within cout x 2^-24 of the sum
     of its terms' magnitudes."""
     import torch
-    mb, hw, cin, cout = 5, (214, 245), 256, 16
+    mb, hw, cin = 5, (214, 245), 256
     st = xp.Stage([relu(-1), conv(0, cin, cout, 1)], mb, 1, hw + (cin,), xp.BF16)
     g = torch.Generator(device="cuda").manual_seed(3)
     W = (torch.randn(cout, cin, generator=g, device="cuda") / 16).to(torch.bfloat16).float()
@@ -366,9 +623,12 @@ def test_wide_data_gradient_tile():
     x = torch.randn(mb, *hw, cin, generator=g, device="cuda").to(torch.bfloat16)
     dy = torch.randn(mb, *hw, cout, generator=g, device="cuda").to(torch.bfloat16)
     dx = torch.empty_like(x)
+    st.set_timing(True)
     st.xpipe_stage_bwd(x, dy, None, dx)
+    torch.cuda.synchronize()
+    assert any(n.startswith("k_conv_gemm_lds<256,256,") for n in st.timing()), list(st.timing())
     ref = (dy.double().reshape(-1, cout) @ W.double()) * (x.reshape(-1, cin) > 0)
-    summed = 16 * 2.0 ** -24 * (dy.double().abs().reshape(-1, cout) @ W.double().abs())
+    summed = cout * 2.0 ** -24 * (dy.double().abs().reshape(-1, cout) @ W.double().abs())
     d = (dx.reshape(-1, cin).double() - ref).abs()
     assert bool((d <= 2.0 ** -8 * (ref.abs() + summed) + summed).all()), float(d.max())
     assert rel_l2(np.asarray(st.get_tensors(st.grad)[0]),
