@@ -2,7 +2,7 @@
 // straight into LDS (forward and data gradient, 16-byte chunk path).
 //
 // What it computes is ConvArgs' definition (xp_kernels.h); the general kernel
-// in k_gemm.hip takes what this one does not (see conv_lds_fits).
+// in k_gemm.hip takes what this one does not, or does faster (see launch_conv_lds).
 #include "xp_device.h"
 #include "xp_lds.h"
 #include "xp_kernels.h"
@@ -573,8 +573,8 @@ int64_t tiles(int64_t rows, int bm, int cols, int bn) { return ((rows + bm - 1) 
 bool fits128(int N) { return 8 * ((N + 127) / 128 * 128) <= 9 * ((N + 63) / 64 * 64); }
 
 // Tile by size, from a sweep of the stages' shapes (us per launch, MI355X):
-//  - up to 32 columns 128x32, up to 64 128x64 (3x3 64->64 at 56x56x100: 46.5,
-//    64x64 tiles 52.5), 65..96 96x96 (3x3 64->96 at 35x35x32: 14.6; 64x128
+//  - up to 32 columns 128x32 (same-grid data gradients of those do not come here), up
+//    to 64 128x64 (3x3 64->64 at 56x56x100: 46.5, 64x64 tiles 52.5), 65..96 96x96 (3x3 64->96 at 35x35x32: 14.6; 64x128
 //    15.5, 128x64 16.0);
 //  - wider: 128x128 on eight waves while it gives 400 tiles (1x1 256->1024 at
 //    14x14x100: 27.4, 64x128 30.6; below that, 3x3 256->256 there, 306 tiles:
@@ -625,9 +625,9 @@ hipError_t pick_step(const ConvArgs& a, int64_t rows, hipStream_t s, int* row_ti
 template <int GM, bool DG>
 hipError_t few(const ConvArgs& a, hipStream_t s, int* row_tiles) {
   if (a.C % 64 != 0) return go<32, 32, 1, 1, 64, 4, true, GM, DG, true>(a, s, row_tiles);
-  if (DG || (int64_t)a.R * a.S * a.C >= 4096)  // (a data gradient comes here from 4096 on)
-    return go<32, 32, 1, 1, 64, 8, false, GM, DG, true>(a, s, row_tiles);
-  if constexpr (!DG) return go<32, 32, 1, 1, 64, 4, false, GM, DG, true>(a, s, row_tiles);
+  if constexpr (!DG)  // (a data gradient comes here from 4096 products on)
+    if ((int64_t)a.R * a.S * a.C < 4096) return go<32, 32, 1, 1, 64, 4, false, GM, DG, true>(a, s, row_tiles);
+  return go<32, 32, 1, 1, 64, 8, false, GM, DG, true>(a, s, row_tiles);
 }
 
 }  // namespace

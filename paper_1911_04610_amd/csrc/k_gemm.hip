@@ -1228,9 +1228,9 @@ static hipError_t conv_dispatch(const ConvArgs& a0, hipStream_t s, int* gr) {
     }
   }
   if constexpr (sizeof(T) == 2) {
-    // What launch_conv_lds leaves: small data gradients, and output channels or
-    // views that are no multiples of 16 bytes, at any size.  From a sweep on MI355X
-    // (tile, stage depth KS, register prefetch depth PF)
+    // What launch_conv_lds leaves: small data gradients, those of up to 32 columns, short
+    // reductions, and output channels or views that are no multiples of 16 bytes, at any
+    // size.  From a sweep on MI355X (tile, stage depth KS, register prefetch depth PF)
     const int taps = a.R * a.S;
     const int ks = flat ? 1 : pick_ks_bf16(a.C, taps);
     // KS counts 32-deep slices for the 16x16 MFMA tiles and 16-deep slices

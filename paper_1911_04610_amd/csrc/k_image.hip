@@ -5,11 +5,13 @@
 // A filter row's S x C values are one run of the NHWC row, so a workgroup stages
 // the input rows of several output rows in LDS (zeros around the image) and takes
 // its operands from there value by value: no index arithmetic and no 2-byte load
-// from memory per value, which bound the general kernels.  Bound
-// now: one 2-byte LDS read per operand value and the epilogue's fp64 sums, at two
-// waves per SIMD (7x7 stride 2 on 224x224x3, 64 channels, micro-batch 100, before /
-// after: forward 409 / 88 us, weight gradient with its reduction 564 / 80 us; the
-// memory floor of either is about 35 us).
+// from memory per value, which bound the general kernels.  Bound now: one 2-byte
+// LDS read per operand value and the epilogue's fp64 sums, at two waves per SIMD (7x7
+// stride 2 on 224x224x3, 64 channels, micro-batch 100, before / after: forward 409 /
+// 88 us, weight gradient with its reduction 560 / 85 us; the memory floor of either is
+// about 35 us).  The weight gradient's sums differ from the general kernel's in order:
+// eight waves' chains per workgroup, each a fraction as long (there 3.7e-7 / 1.5e-7 of
+// the gradient off 64-bit sums, over smaller maps 6.5e-8 / 5.5e-8).
 #include "xp_device.h"
 #include "xp_lds.h"
 #include "xp_kernels.h"

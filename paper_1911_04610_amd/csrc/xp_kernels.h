@@ -152,8 +152,8 @@ struct WgradArgs {
 // grid_rows (optional) receives the number of row tiles of the launch
 hipError_t launch_conv_gemm(int dtype, const ConvArgs& a, hipStream_t s, int* grid_rows = nullptr);
 // the bf16 kernel that copies its operands straight into LDS (k_conv.hip):
-// false when the call is not one it is written for or has too few tiles, and
-// then nothing is launched; else the launch's status in *e
+// false when the call is not one it is written for, or one that the general kernel
+// does faster, and then nothing is launched; else the launch's status in *e
 bool launch_conv_lds(const ConvArgs& a, hipStream_t s, int* row_tiles, hipError_t* e);
 // the bf16 kernels for images of a few channels (k_image.hip), likewise; the
 // weight gradient leaves *splits (at most a.splits) partials in a.part
