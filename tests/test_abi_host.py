@@ -121,6 +121,17 @@ def test_stage_create_checks_arguments_before_touching_the_device():
     assert b"workspace" in L.xpipe_last_error()
 
 
+@pytest.mark.parametrize("k,cin,cout,stride,mb,hw,nbytes", [
+    (1, 64, 256, 1, 100, 56, 346391296), (3, 96, 96, 1, 32, 35, 89205504), (1, 256, 1024, 1, 100, 14, 107021056),
+    (7, 3, 64, 2, 100, 224, 359794432), (3, 256, 512, 1, 32, 8, 67896064)])
+def test_workspace_of_a_layer_stays_what_programs_allocated(k, cin, cout, stride, mb, hw, nbytes):
+    """A program that keeps a workspace of a fixed size finds it large enough: the bytes
+    hold the activations and the weight gradient's partial sums, whose count is a rule
+    of the sizes (a plan with other splits needed 7% to 24% more for two of these)."""
+    layers = [dict(kind="conv", inputs=[-1], cin=cin, cout=cout, k=k, kw=k, stride=stride, pad="same", bias=False)]
+    assert xp.xpipe_stage_query(layers, mb, (hw, hw, cin), xp.BF16)[1] == nbytes
+
+
 def test_flat_entry_points_check_arguments_on_the_host():
     L = xp.lib()
     hp = xp.Hyper().c(1)
