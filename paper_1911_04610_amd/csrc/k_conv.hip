@@ -574,8 +574,8 @@ bool fits128(int N) { return 8 * ((N + 127) / 128 * 128) <= 9 * ((N + 63) / 64 *
 
 // Tile by size, from a sweep of the stages' shapes (us per launch, MI355X):
 //  - up to 32 columns 128x32 (same-grid data gradients of those do not come here), up
-//    to 64 128x64 (3x3 64->64 at 56x56x100: 46.5, 64x64 tiles 52.5), 65..96 96x96 (3x3 64->96 at 35x35x32: 14.6; 64x128
-//    15.5, 128x64 16.0);
+//    to 64 128x64 (3x3 64->64 at 56x56x100: 46.5, 64x64 tiles 52.5), 65..96 96x96
+//    (3x3 64->96 at 35x35x32: 14.6; 64x128 15.5, 128x64 16.0);
 //  - wider: 128x128 on eight waves while it gives 400 tiles (1x1 256->1024 at
 //    14x14x100: 27.4, 64x128 30.6; below that, 3x3 256->256 there, 306 tiles:
 //    41.3 against 38.1), then 64x128, then 64x64 (3x3 512->512 at 7x7x100:

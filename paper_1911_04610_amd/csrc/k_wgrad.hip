@@ -12,10 +12,11 @@ namespace xp {
 
 namespace {
 
-// LDS tiles hold one row per pixel, WID (64 or 128) elements wide, without padding: the 16-byte chunk c of row p sits at position c ^ swz(p), which
-// moves four consecutive rows (what 16 lanes of a transposing read touch) to
-// different 64-byte bank groups.  swz is the same for all rows that a lane
-// copies, and for all that it reads.
+// LDS tiles hold one row per pixel, WID (64 or 128) elements wide, without padding:
+// the 16-byte chunk c of row p sits at position c ^ swz(p), which moves four
+// consecutive rows (what 16 lanes of a transposing read touch) to different 64-byte
+// bank groups.  swz is the same for all rows that a lane copies, and for all that it
+// reads.
 template <int WID>
 XP_DEV int swz(int row) {
   static_assert(WID == 64 || WID == 128, "tile width");
